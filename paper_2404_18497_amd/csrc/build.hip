@@ -1725,6 +1725,17 @@ hipError_t spin_sync(hipStream_t st) {
   }
 }
 
+// What the launch rule of the search asks of the device, and the average bucket size.
+hipError_t search_device_limits(SearchArgs& sa, double bucket_keys) {
+  int dev = 0, cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  sa.cus = (uint32_t)cus;
+  sa.lds_limit = (uint32_t)max_lds_per_group();
+  sa.bucket_keys = (float)bucket_keys;
+  return e;
+}
+
 void configure_pool_once() {
   static std::once_flag once;
   std::call_once(once, [] {
@@ -2072,6 +2083,7 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
   const uint32_t mm = (uint32_t)std::max<uint64_t>(max_m, 1);
   const uint32_t mb = std::max<uint32_t>(hmaxb, 1);
   size_search_lds(sa, mm, mb, B, wide);
+  PHOBIC_HIP(search_device_limits(sa, (double)n / ((double)K * B)));
   if (wide && sa.wave_lds > max_lds_per_group())
     return fail(PHOBIC_E_CAPACITY, "a partition of " + std::to_string(mm) + " slots does not fit the LDS of one workgroup");
   sa.owner = nullptr;
@@ -2780,6 +2792,7 @@ phobic_status build_batch_impl(const uint64_t* const* keys, const uint64_t* coun
   sa.B = B;
   const uint32_t mm = std::max<uint32_t>(hinfo[2], 1), mb = std::max<uint32_t>(hinfo[1], 1);
   size_search_lds(sa, mm, mb, B, false);
+  PHOBIC_HIP(search_device_limits(sa, (double)Ntot / ((double)Ktot * B)));
   sa.owner = owner;
   sa.Kbase = d_Kbase;
   sa.Kt = d_Kt;

@@ -31,6 +31,11 @@ struct SearchArgs {
   uint32_t max_bucket;    // the largest bucket (keys) the LDS layout holds
   uint32_t wide;          // 1: pilot row in global memory and F2 unshifted (wide partitions, one MPHF)
   uint32_t wave_lds;      // bytes of LDS per wavefront (multiple of 16), see size_search_lds
+  uint32_t own_words;     // team search: entries of the claim table (a power of two)
+  uint32_t team_scr;      // team search: 32-bit words of a wavefront's repeat scratch (multiple of 4)
+  uint32_t lds_limit;     // bytes of LDS one workgroup may use
+  uint32_t cus;           // compute units of the device
+  float bucket_keys;      // keys per bucket, on average
   // several MPHFs at once: partition J belongs to MPHF owner[J], whose partitions start at
   // Kbase[t] (K_t of them) and whose pilots start at B * Kbase[t]; null for a single MPHF
   const uint32_t* owner;
@@ -74,6 +79,25 @@ inline void size_search_lds(SearchArgs& sa, uint32_t mm, uint32_t mb, uint32_t B
   const uint32_t f2_copies = wide ? 1u : 2u;
   sa.wave_lds = ((sa.f2_words * f2_copies + sa.scr_words + sa.rb_cap + sa.bl_cap) * 4 + sa.cm_cap * 8 +
                  kSearchCtxBytes + 15) & ~15u;
+}
+
+// Team search (search_team.h): up to kTeamMaxWaves wavefronts per partition; kTeamCtlWords control
+// words, the bitmaps, a claim table with an entry per slot up to kTeamClaims, and per wavefront a
+// repeat scratch of up to kTeamScratchBits and a position buffer.
+constexpr uint32_t kTeamMaxWaves = 16;
+constexpr uint32_t kTeamCtlWords = 144;
+constexpr uint32_t kTeamClaims = 4096;
+constexpr uint32_t kTeamScratchBits = 8192;
+constexpr uint32_t kTeamShiftSlots = 1u << 16;  // smaller tables keep a shifted copy of the bitmap
+
+// Sets the fields of the team's LDS layout (after size_search_lds); its bytes for W wavefronts.
+inline size_t size_team_lds(SearchArgs& sa, uint32_t W) {
+  auto up4 = [](uint32_t v) { return (v + 3) & ~3u; };
+  sa.own_words = 64;
+  while (sa.own_words < sa.max_m && sa.own_words < kTeamClaims) sa.own_words *= 2;
+  sa.team_scr = sa.max_m > kTeamScratchBits ? kTeamScratchBits / 32 : up4((sa.max_m + 31) / 32);
+  return 4 * ((size_t)kTeamCtlWords + (size_t)sa.f2_words * (sa.max_m < kTeamShiftSlots ? 2 : 1) + sa.own_words +
+              (size_t)W * (sa.team_scr + sa.rb_cap));
 }
 
 // Error bit of a partition or bucket larger than the search's LDS layout was sized for (the build

@@ -6,6 +6,7 @@
 #include <cstdint>
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "phobic_internal.h"
 #include "search.h"
@@ -55,8 +56,8 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
   return ((uint64_t)uniform((uint32_t)(v >> 32)) << 32) | uniform((uint32_t)v);
 }
 __device__ __forceinline__ uint64_t lane_value64(uint64_t v, uint32_t lane) {
-  return ((uint64_t)__builtin_amdgcn_readlane((uint32_t)(v >> 32), lane) << 32) |
-         __builtin_amdgcn_readlane((uint32_t)v, lane);
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((uint32_t)(v >> 32), lane) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((uint32_t)v, lane);  // the builtin returns int
 }
 
 // Encoded positions: the high half of a code is the byte offset, from F2, of the load that starts at
@@ -768,6 +769,8 @@ __device__ void search_partition(const SearchArgs& a, uint64_t j, uint32_t* F2, 
   }
 }
 
+#include "search_team.h"
+
 // ---------------------------------------------------------------------------------------------
 // Launch order.  A partition's search time is dominated by per-bucket work (about proportional to
 // its buckets and keys) plus the seeds its biggest buckets need before their positions stop
@@ -909,6 +912,16 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(8, 
   }
 }
 
+// A team of blockDim.x / 64 wavefronts per partition.
+template <bool kShift, bool kFew>
+__global__ __launch_bounds__(64 * kTeamMaxWaves) void k_search_team(SearchArgs a) {
+  extern __shared__ __align__(16) uint32_t lds32[];
+  const uint64_t x = blockIdx.x;
+  if (x >= a.K) return;
+  const uint64_t j = a.order ? (uint64_t)uniform(a.order[x]) : x;
+  search_team<kShift, kFew>(a, j, lds32, uniform(threadIdx.x >> 6), threadIdx.x & 63, uniform(blockDim.x >> 6));
+}
+
 // ---------------------------------------------------------------------------------------------
 // Search launch shape
 // ---------------------------------------------------------------------------------------------
@@ -973,14 +986,58 @@ hipError_t order_partitions(SearchArgs& sa, uint32_t* order, uint32_t* scratch, 
   return hipGetLastError();
 }
 
+template <bool kShift, bool kFew>
+hipError_t launch_team(SearchArgs& sa, uint64_t items, uint32_t W, size_t lds, hipStream_t st) {
+  sa.queue = nullptr;
+  (void)allow_lds(k_search_team<kShift, kFew>, lds);
+  hipLaunchKernelGGL((k_search_team<kShift, kFew>), dim3((uint32_t)items), dim3(64 * W), lds, st, sa);
+  return hipGetLastError();
+}
+
+// Wavefronts per partition under the default shape (1: the one-wavefront kernels).  A team pays while the
+// launch leaves wavefront slots empty, and longer the more pilots a bucket tries (keys per bucket,
+// lambda): it issues 1.5 to 3 times the instructions per partition.  A CU holds three teams of eight
+// or six of four (77 registers).  Search times in us, P = 2500, one wavefront / 4 / 8 / 16 per partition:
+//   lambda 5:  160 partitions 457/284/218/233, 520: 631/365/331/575, 1500: 491/497/613/1189, 3000: 533/908
+//   lambda 7:  1: 449/245/223/263, 160: 598/327/312/363, 520: 704/389/394/763, 1000: 829/459/616/1177,
+//              2000: 921/758/1018, 3000: 1291/1024/1455, 4000: 941/1646
+//   lambda 9:  160: 1937/836/697/769, 520: 2231/986/909/1712, 1000: 2466/1089/1329/2621,
+//              2000: 3458/1949/2322, 3000: 3461/2417/3335, 4000: 2680/2883/4018
+//   lambda 11: 8000: 22738/20062/24754
+//   lambda 12: 160: 38796/9310/5955/4856, 520: 51465/13386/8625/8471, 1000: 53308/12325/9866/12746,
+//              2000: 50323/17567/16381/26222, 4000: 52056/27472/28338, 16000: 106844/86692/99983,
+//              40 000: 175300/205800/242200
+//   lambda 7, larger P: 10 000 (100 partitions) 1622/1025/781/764, (1000) 1855/1404/1632/2762;
+//              20 000 (500) 2579/2157/1744/2478; 50 000 (200) 6020/4475/3236/2888; 100 000 (100)
+//              11923/8660/6366/5641
+uint32_t team_waves(const SearchArgs& sa, uint64_t items) {
+  const uint64_t c = sa.cus;
+  const float l = sa.bucket_keys;
+  if (items <= c) return l >= 10.8f || sa.max_m > kTeamScratchBits ? 16 : 8;
+  if (items <= 3 * c) return 8;
+  if (items <= 6 * c) return l >= 10.8f ? 8 : 4;
+  if (items <= 12 * c) return l >= 6.0f ? 4 : 1;
+  if (items <= 16 * c) return l >= 10.0f ? 4 : 1;
+  if (items <= 32 * c) return l >= 10.8f ? 4 : 1;
+  return items <= 64 * c && l >= 11.8f ? 4 : 1;
+}
+
 hipError_t launch_search(SearchArgs& sa, uint64_t items, hipStream_t st, unsigned long long* queue) {
+  const phobic_search_config cfg = search_config();
+  uint32_t W = cfg.waves_per_group == 1 && cfg.groups_per_cu == 0 ? team_waves(sa, items) : 1;
+  while (W > 1 && size_team_lds(sa, W) > sa.lds_limit) W /= 2;
+  if (W > 1) {
+    const size_t lds = size_team_lds(sa, W);
+    if (sa.max_m <= kTeamScratchBits) return launch_team<true, true>(sa, items, W, lds, st);
+    return sa.max_m < kTeamShiftSlots ? launch_team<true, false>(sa, items, W, lds, st)
+                                      : launch_team<false, false>(sa, items, W, lds, st);
+  }
   if (sa.wide) {
     sa.queue = nullptr;
     (void)allow_lds(k_search_wide, sa.wave_lds);
     hipLaunchKernelGGL(k_search_wide, dim3((uint32_t)items), dim3(64), sa.wave_lds, st, sa);
     return hipGetLastError();
   }
-  const phobic_search_config cfg = search_config();
   // tables of more than 4096 slots need scans of several passes
   return sa.max_m > 4096 ? launch_search_m<true>(sa, items, cfg, st, queue)
                          : launch_search_m<false>(sa, items, cfg, st, queue);
