@@ -13,7 +13,6 @@
 #include <cstring>
 #include <string>
 #include <vector>
-#include <type_traits>
 
 #include "phobic_internal.h"
 
@@ -33,94 +32,82 @@ __device__ __forceinline__ uint64_t sel_start(uint64_t e, uint64_t ta, uint32_t&
   return (e & 0xFFFFFFFFULL) + (sub ? rel : 0u);
 }
 
-// High part q of value t of the unary stream: q = (position of one t) - (position of one t-1) - 1,
-// with one -1 at position -1.  The select entry of one t-1 is read without a preceding branch, so
-// its load can issue as soon as t is known.
-__device__ __forceinline__ uint64_t unary_high(const uint64_t* __restrict__ un, const uint64_t* __restrict__ sel,
-                                               uint64_t t) {
-  const uint64_t ta = t ? t - 1 : 0;
-  const uint64_t e = sel[ta / kSelBlock];
-  uint64_t prev;  // position of one t-1, or UINT64_MAX for t = 0
-  uint64_t word;
-  uint64_t bits;
-  if (t == 0) {
-    prev = ~0ULL;
-    word = 0;
-    bits = un[0];
-  } else {
-    uint32_t r;
-    const uint64_t start = sel_start(e, ta, r);
-    word = start >> 6;
-    bits = un[word] & (~0ULL << (start & 63));
-    for (;;) {
-      uint32_t c = __popcll(bits);
-      if (r < c) break;
-      r -= c;
-      bits = un[++word];
-    }
-    prev = word * 64 + select_in_word(bits, r);
-    // continue after prev for the next one
-    const uint32_t b = (uint32_t)(prev & 63);
-    bits = b == 63 ? 0 : (bits & (~0ULL << (b + 1)));
-  }
-  while (bits == 0) bits = un[++word];
-  const uint64_t cur = word * 64 + (uint32_t)(__ffsll((long long)bits) - 1);
-  return cur - prev - 1;
+// The lookups are bound by their cache requests, so every field is read with one load: sections are
+// read at 4-byte steps, where 8 bytes hold any field of up to 33 bits and 12 any pair of up to 65.
+// Each section ends in a zero word, so the bytes past the last field are inside the image.  With aligned
+// 8-byte reads and a second one where a field straddles, and the unary stream read a word at a time,
+// the same lookups took longer: 1M keys of a 10^8-key table 38.9 -> 35.2 us, 1000 keys of a 10^6-key
+// table 9.2 -> 8.0 us (a launch in a queue of them), all 10^8 keys of a build 3.07 -> 2.62 ms.
+typedef uint64_t u64_at4 __attribute__((aligned(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_at4 __attribute__((aligned(4)));
+
+// The field of w <= 32 bits at bit pos.
+__device__ __forceinline__ uint32_t field32(const uint64_t* __restrict__ sec, uint64_t pos, uint32_t w) {
+  const uint64_t v = *(const u64_at4*)((const uint32_t*)sec + (pos >> 5)) >> (pos & 31);
+  return (uint32_t)(v & ((1ULL << w) - 1));
 }
 
-// The residues of offsets j and j + 1: adjacent fields of woff <= 32 bits lie in one word or in two
-// consecutive ones (the section's trailing pad word keeps idx + 1 inside it); the lookup is bound by
-// its memory requests, so the second word is read only when the pair straddles.
+// The residues of offsets j and j + 1, adjacent fields of woff bits (the same for all lookups).
 __device__ __forceinline__ void offset_pair(const uint64_t* __restrict__ offs, uint64_t j, uint32_t woff,
                                             uint64_t& r0, uint64_t& r1) {
+  const uint64_t pos = j * woff;
+  const uint64_t mask = (1ULL << woff) - 1;
   if (woff == 0) {
     r0 = r1 = 0;
+  } else if (woff <= 16) {
+    const uint64_t v = *(const u64_at4*)((const uint32_t*)offs + (pos >> 5)) >> (pos & 31);
+    r0 = v & mask;
+    r1 = (v >> woff) & mask;
   } else if (woff <= 32) {
-    const uint64_t pos = j * woff, idx = pos >> 6;
-    const uint32_t sh = (uint32_t)(pos & 63);
-    const uint64_t w0 = offs[idx];
-    const uint64_t w1 = sh + 2 * woff > 64 ? offs[idx + 1] : 0;  // only a straddling pair reads it
-    const uint64_t lo64 = sh ? ((w0 >> sh) | (w1 << (64 - sh))) : w0;  // bits [pos, pos + 64)
-    const uint64_t mask = (1ULL << woff) - 1;
-    r0 = lo64 & mask;
-    r1 = (lo64 >> woff) & mask;
+    const uint32_t* p = (const uint32_t*)offs + (pos >> 5);
+    const uint32_t sh = (uint32_t)(pos & 31);
+    const uint64_t lo = *(const u64_at4*)p;
+    const uint64_t v = sh ? (lo >> sh) | ((uint64_t)p[2] << (64 - sh)) : lo;
+    r0 = v & mask;
+    r1 = (v >> woff) & mask;
   } else {
-    r0 = get_bits(offs, j * woff, woff);
-    r1 = get_bits(offs, (j + 1) * woff, woff);
+    r0 = get_bits(offs, pos, woff);
+    r1 = get_bits(offs, pos + woff, woff);
   }
 }
 
-__device__ __forceinline__ uint64_t query_code(const QueryArgs& a, uint64_t hi, uint64_t lo) {
-  if (a.n == 0) return 0;
-  const uint64_t* __restrict__ T = a.table;
-  const uint64_t* __restrict__ enc = a.img + a.sec_enc;
-  const uint64_t* __restrict__ offs = a.img + a.sec_off;
-  // The pilot's fields depend on (i, j) only, not on the offsets: the offset pair, the low bits and
-  // the select sample are independent reads that are in flight together.
-  const uint64_t j = __umul64hi(hi, a.K);
-  const uint32_t i = bucket_of(lo, T, a.B);
-  const uint64_t e = enc[i];
-  const uint32_t w = (uint32_t)(e & 0xFF);
-  uint64_t r0, r1;
-  offset_pair(offs, j, a.woff, r0, r1);
-  uint64_t p = get_bits(a.img + a.sec_data, (e >> 8) + j * w, w);
-  if (a.coding == PHOBIC_IC_RICE && i >= a.ncompact) {  // encoders below ncompact are Compact
-    const uint64_t q = unary_high(a.img + a.sec_unary, a.img + a.sec_sel, (uint64_t)(i - a.ncompact) * a.K + j);
-    p |= q << w;
+// 128 bits of the unary stream from bit `base` (a multiple of 32) on, and how far the search for a value
+// has come: `need` ones of the window precede the value's own one, `last` is the position of the one
+// before the window (of value t - 1, if need is 0).
+struct UnaryWindow {
+  uint64_t lo, hi, last;
+  uint64_t base;
+  uint32_t need;
+};
+__device__ __forceinline__ void unary_load(const uint64_t* __restrict__ un, UnaryWindow& w) {
+  const u32x4 v = *(const u32x4_at4*)((const uint32_t*)un + (w.base >> 5));
+  w.lo = ((uint64_t)v.y << 32) | v.x;
+  w.hi = ((uint64_t)v.w << 32) | v.z;
+}
+// Whether the value's one lies past the window; the search then moves on by a window (not loaded yet).
+__device__ __forceinline__ bool unary_past(UnaryWindow& w) {
+  const uint32_t c = __popcll(w.lo) + __popcll(w.hi);
+  if (w.need < c) return false;
+  if (c) w.last = w.base + (w.hi ? 127 - __clzll((long long)w.hi) : 63 - __clzll((long long)w.lo));
+  w.need -= c;
+  w.base += 128;
+  return true;
+}
+// q = distance of the value's one from the one before it, less one.
+__device__ __forceinline__ uint32_t unary_value(const UnaryWindow& w) {
+  uint64_t lo = w.lo, hi = w.hi, prev = w.last;
+  if (w.need) {  // the one before lies in the window: number need - 1 of it
+    const uint32_t c0 = __popcll(lo), k = w.need - 1;
+    const bool up = k >= c0;
+    const uint32_t b = select_in_word(up ? hi : lo, up ? k - c0 : k);
+    const uint64_t above = b == 63 ? 0 : ~0ULL << (b + 1);
+    prev = w.base + b + (up ? 64 : 0);
+    lo = up ? 0 : lo & above;
+    hi = up ? hi & above : hi;
   }
-  const uint64_t o0 = expected_offset(j, a.R) + (uint64_t)a.dmin + r0;
-  const uint64_t o1 = expected_offset(j + 1, a.R) + (uint64_t)a.dmin + r1;
-  const uint32_t m = (uint32_t)(o1 - o0);
-  if (m == 0) return o0 < a.n ? o0 : a.n - 1;  // only a non-member reaches an empty partition
-  // pilots are at most 2^32 - 1, so 32-bit division is exact
-  const uint32_t p32 = (uint32_t)p;
-  const uint32_t s = p32 / m;
-  const uint32_t d = p32 - s * m;
-  uint32_t pos = pos_hash(fingerprint(hi, lo), (uint64_t)(s + 1) * kPhi64, m) + d;
-  if (pos >= m) pos -= m;
-  const uint64_t g = o0 + pos;
-  if (g < a.n) return g;
-  return get_bits(a.img + a.sec_remap, (g - a.n) * a.wremap, a.wremap);
+  const uint64_t cur = w.base + (lo ? (uint32_t)__ffsll((long long)lo) - 1 : 63 + (uint32_t)__ffsll((long long)hi));
+  return (uint32_t)(cur - prev - 1);
 }
 
 // bucket_of over a table held in 64-bit words, or in 32-bit words where the last point, 2^32, reads
@@ -140,8 +127,7 @@ __device__ __forceinline__ uint32_t bucket_of_tab(uint64_t lo, const uint32_t* _
 
 // kN lookups per thread in lockstep: every stage issues the reads of all kN lookups before any of
 // them is consumed, so one wavefront keeps kN times as many independent cache-line reads in flight
-// (the query is bound by the latency of its chain of dependent reads, not by bandwidth).  Same
-// arithmetic as query_code.
+// (the query is bound by the latency of its chain of dependent reads, not by bandwidth).
 template <int kN, typename TabT>
 __device__ __forceinline__ void query_codes(const QueryArgs& a, const TabT* __restrict__ T,
                                             const uint64_t* __restrict__ E, const uint64_t (&hi)[kN],
@@ -150,8 +136,8 @@ __device__ __forceinline__ void query_codes(const QueryArgs& a, const TabT* __re
   const uint64_t* __restrict__ un = a.img + a.sec_unary;
   const uint64_t* __restrict__ sel = a.img + a.sec_sel;
   const bool rice = a.coding == PHOBIC_IC_RICE;
-  uint64_t j[kN], e[kN], p[kN], r0[kN], r1[kN];
-  uint32_t i[kN];
+  uint64_t j[kN], e[kN], r0[kN], r1[kN];
+  uint32_t i[kN], p[kN];  // pilots are at most 2^32 - 1
 #pragma unroll
   for (int q = 0; q < kN; q++) {
     j[q] = __umul64hi(hi[q], a.K);
@@ -162,73 +148,57 @@ __device__ __forceinline__ void query_codes(const QueryArgs& a, const TabT* __re
   // offsets, low bits and select samples: independent of each other.  A lookup whose encoder is
   // Rice (u) reads the unary stream at its value t = (i - ncompact) K + j; one of a Compact encoder
   // (all of a Compact image, the first ncompact of a mixed one) is done with its field.
-  uint64_t t[kN], ta[kN], sample[kN];
+  uint64_t t[kN], sample[kN];
   bool u[kN];
 #pragma unroll
   for (int q = 0; q < kN; q++) {
     offset_pair(offs, j[q], a.woff, r0[q], r1[q]);
     const uint32_t w = (uint32_t)(e[q] & 0xFF);
-    p[q] = get_bits(a.img + a.sec_data, (e[q] >> 8) + j[q] * w, w);
+    p[q] = field32(a.img + a.sec_data, (e[q] >> 8) + j[q] * w, w);
     u[q] = rice && i[q] >= a.ncompact;
     t[q] = u[q] ? (uint64_t)(i[q] - a.ncompact) * a.K + j[q] : 0;
-    ta[q] = t[q] ? t[q] - 1 : 0;
-    sample[q] = u[q] ? sel[ta[q] / kSelBlock] : 0;
+    sample[q] = u[q] ? sel[(t[q] ? t[q] - 1 : 0) / kSelBlock] : 0;
   }
   if (rice) {
-    uint64_t word[kN], bits[kN], prev[kN];
-    uint32_t r[kN];
-    bool found[kN];
+    UnaryWindow w[kN];
+    bool more[kN];
 #pragma unroll
     for (int q = 0; q < kN; q++) {
-      const uint64_t start = sel_start(sample[q], ta[q], r[q]);
-      word[q] = t[q] ? start >> 6 : 0;
-      bits[q] = u[q] ? un[word[q]] : 1;  // a Compact lookup keeps a set bit: no reads below
-      if (t[q]) bits[q] &= ~0ULL << (start & 63);
-      found[q] = t[q] == 0;
+      uint32_t r = 0;
+      const uint64_t start = t[q] ? sel_start(sample[q], t[q] - 1, r) : 0;
+      w[q].base = start & ~31ULL;
+      w[q].need = t[q] ? r + 1 : 0;  // ones from `start` on before the value's own
+      w[q].last = ~0ULL;             // value 0: the one before is at -1
+      w[q].lo = w[q].hi = 1;         // a Compact lookup is done
+      if (u[q]) {
+        unary_load(un, w[q]);
+        w[q].lo &= ~0ULL << (start & 31);
+      }
     }
-    // the one of value t - 1: skip r ones from the sample
-    for (bool more = true; more;) {
-      more = false;
+    // most windows hold the value's one; the others go on
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < kN; q++) {
+      more[q] = u[q] && unary_past(w[q]);
+      any |= more[q];
+    }
+    while (any) {
+      any = false;
+#pragma unroll
+      for (int q = 0; q < kN; q++)
+        if (more[q]) unary_load(un, w[q]);
 #pragma unroll
       for (int q = 0; q < kN; q++) {
-        if (!found[q]) {
-          const uint32_t c = __popcll(bits[q]);
-          if (r[q] < c) {
-            found[q] = true;
-          } else {
-            r[q] -= c;
-            bits[q] = un[++word[q]];
-            more = true;
-          }
-        }
+        more[q] = more[q] && unary_past(w[q]);
+        any |= more[q];
       }
     }
 #pragma unroll
-    for (int q = 0; q < kN; q++) {
-      if (t[q] == 0) {
-        prev[q] = ~0ULL;
-      } else {
-        prev[q] = word[q] * 64 + select_in_word(bits[q], r[q]);
-        const uint32_t b = (uint32_t)(prev[q] & 63);
-        bits[q] = b == 63 ? 0 : (bits[q] & (~0ULL << (b + 1)));
+    for (int q = 0; q < kN; q++)
+      if (u[q]) {
+        const uint32_t b = (uint32_t)(e[q] & 0xFF);  // 32 bits wide: the high part is 0
+        p[q] |= b < 32 ? unary_value(w[q]) << b : 0u;
       }
-    }
-    // the one of value t: the next set bit
-    for (bool more = true; more;) {
-      more = false;
-#pragma unroll
-      for (int q = 0; q < kN; q++) {
-        if (bits[q] == 0) {
-          bits[q] = un[++word[q]];
-          more = true;
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < kN; q++) {
-      const uint64_t cur = word[q] * 64 + (uint32_t)(__ffsll((long long)bits[q]) - 1);
-      if (u[q]) p[q] |= (cur - prev[q] - 1) << (uint32_t)(e[q] & 0xFF);
-    }
   }
 #pragma unroll
   for (int q = 0; q < kN; q++) {
@@ -239,9 +209,8 @@ __device__ __forceinline__ void query_codes(const QueryArgs& a, const TabT* __re
       res[q] = o0 < a.n ? o0 : a.n - 1;
       continue;
     }
-    const uint32_t p32 = (uint32_t)p[q];
-    const uint32_t s = p32 / m;
-    const uint32_t d = p32 - s * m;
+    const uint32_t s = p[q] / m;
+    const uint32_t d = p[q] - s * m;
     uint32_t pos = pos_hash(fingerprint(hi[q], lo[q]), (uint64_t)(s + 1) * kPhi64, m) + d;
     if (pos >= m) pos -= m;
     const uint64_t g = o0 + pos;
@@ -252,11 +221,11 @@ __device__ __forceinline__ void query_codes(const QueryArgs& a, const TabT* __re
 constexpr int kQN = 4;
 constexpr uint32_t kQEncLds = 1024;  // encoders the LDS-staged query holds
 
-// Thread x handles keys x, x + stride, ..., kQN of them per round.  kLds: the bucket-function table
-// (as 32-bit words) and the encoder words (B <= kQEncLds) are read from LDS, where the workgroup
-// copies them first: a wavefront's read of either touches dozens of cache lines, and the lookup is
-// bound by its cache requests (10.9 KB per workgroup at B = 358, 7% off the query time at 10^8 keys).
-template <bool kLds, typename TabT = typename std::conditional<kLds, uint32_t, uint64_t>::type>
+// Thread x handles keys x, x + stride, ..., kQN of them per round.  The bucket-function table (as 32-bit
+// words) and, if kEnc (B <= kQEncLds), the encoder words are read from LDS, where the workgroup copies
+// them first: a wavefront's read of either touches dozens of cache lines, and the lookup is bound by
+// its cache requests (10.9 KB per workgroup at B = 358, 7% off the query time at 10^8 keys).
+template <bool kEnc>
 __global__ __launch_bounds__(kQBlock) void k_query_u64(QueryArgs a, const uint64_t* __restrict__ keys, uint64_t n,
                                                         uint64_t* __restrict__ out) {
   if (a.n == 0) {
@@ -264,16 +233,13 @@ __global__ __launch_bounds__(kQBlock) void k_query_u64(QueryArgs a, const uint64
       out[x] = 0;
     return;
   }
-  __shared__ TabT sT[kLds ? kTableIntervals + 1 : 1];
-  __shared__ uint64_t sE[kLds ? kQEncLds : 1];
+  __shared__ uint32_t sT[kTableIntervals + 1];
+  __shared__ uint64_t sE[kEnc ? kQEncLds : 1];
   const uint64_t* E = a.img + a.sec_enc;
-  if (kLds) {
-    for (uint32_t x = threadIdx.x; x <= kTableIntervals; x += kQBlock) sT[x] = (TabT)a.table[x];
+  for (uint32_t x = threadIdx.x; x <= kTableIntervals; x += kQBlock) sT[x] = (uint32_t)a.table[x];
+  if (kEnc)
     for (uint32_t x = threadIdx.x; x < a.B; x += kQBlock) sE[x] = E[x];
-    __syncthreads();
-    E = sE;
-  }
-  const TabT* T = kLds ? (const TabT*)sT : (const TabT*)a.table;
+  __syncthreads();
   const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
   for (uint64_t x0 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; x0 < n; x0 += stride * kQN) {
     uint64_t hi[kQN], lo[kQN], res[kQN];
@@ -282,7 +248,10 @@ __global__ __launch_bounds__(kQBlock) void k_query_u64(QueryArgs a, const uint64
       const uint64_t x = x0 + q * stride;
       hash_key_u64(keys[x < n ? x : x0], a.seed, hi[q], lo[q]);
     }
-    query_codes<kQN, TabT>(a, T, E, hi, lo, res);
+    if (kEnc)
+      query_codes<kQN>(a, (const uint32_t*)sT, (const uint64_t*)sE, hi, lo, res);
+    else
+      query_codes<kQN>(a, (const uint32_t*)sT, E, hi, lo, res);
 #pragma unroll
     for (int q = 0; q < kQN; q++) {
       const uint64_t x = x0 + q * stride;
@@ -295,10 +264,15 @@ __global__ __launch_bounds__(kQBlock) void k_query_str(QueryArgs a, const uint8_
                                                        const uint64_t* __restrict__ offs, uint64_t n,
                                                        uint64_t* __restrict__ out) {
   for (uint64_t x = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; x < n; x += (uint64_t)gridDim.x * blockDim.x) {
+    if (a.n == 0) {
+      out[x] = 0;
+      continue;
+    }
     const uint64_t s0 = offs[x], s1 = offs[x + 1];
-    uint64_t hi, lo;
-    hash_key_str(bytes + s0, s1 - s0, a.seed, hi, lo);
-    out[x] = query_code(a, hi, lo);
+    uint64_t hi[1], lo[1], res[1];
+    hash_key_str(bytes + s0, s1 - s0, a.seed, hi[0], lo[0]);
+    query_codes<1>(a, a.table, a.img + a.sec_enc, hi, lo, res);
+    out[x] = res[0];
   }
 }
 
@@ -314,15 +288,14 @@ constexpr uint32_t kMultiItems = 4;
 // Lookups first + t kQBlock + threadIdx.x (t < kMultiItems) of request jb, in lockstep (query_codes).
 // The block exists for the request, so its first lookup is in range and stands in for those past the
 // end.
-template <typename TabT>
-__device__ __forceinline__ void multi_items(const QueryJob& jb, const TabT* T, const uint64_t* E, uint64_t first) {
+__device__ __forceinline__ void multi_items(const QueryJob& jb, const uint32_t* T, const uint64_t* E, uint64_t first) {
   uint64_t hi[kMultiItems], lo[kMultiItems], res[kMultiItems];
 #pragma unroll
   for (uint32_t t = 0; t < kMultiItems; t++) {
     const uint64_t x = first + t * kQBlock + threadIdx.x;
     hash_key_u64(jb.keys[x < jb.n ? x : first], jb.qa.seed, hi[t], lo[t]);
   }
-  query_codes<(int)kMultiItems, TabT>(jb.qa, T, E, hi, lo, res);
+  query_codes<(int)kMultiItems>(jb.qa, T, E, hi, lo, res);
 #pragma unroll
   for (uint32_t t = 0; t < kMultiItems; t++) {
     const uint64_t x = first + t * kQBlock + threadIdx.x;
@@ -356,13 +329,14 @@ __global__ __launch_bounds__(kQBlock) void k_query_multi(const QueryJob* __restr
     return;
   }
   const uint64_t* E = jb.qa.img + jb.qa.sec_enc;
+  for (uint32_t x = threadIdx.x; x <= kTableIntervals; x += kQBlock) sT[x] = (uint32_t)jb.qa.table[x];
   if (jb.qa.B <= kQEncLds) {
-    for (uint32_t x = threadIdx.x; x <= kTableIntervals; x += kQBlock) sT[x] = (uint32_t)jb.qa.table[x];
     for (uint32_t x = threadIdx.x; x < jb.qa.B; x += kQBlock) sE[x] = E[x];
     __syncthreads();
-    multi_items<uint32_t>(jb, sT, sE, first);
+    multi_items(jb, sT, sE, first);
   } else {
-    multi_items<uint64_t>(jb, jb.qa.table, E, first);
+    __syncthreads();
+    multi_items(jb, sT, E, first);
   }
 }
 
