@@ -203,26 +203,26 @@ __device__ __forceinline__ void hash_key_u64(uint64_t key, uint64_t seed, uint64
   lo = mix_b(key ^ seed ^ kSqrt2);
 }
 
-// The nb <= 8 bytes at p as a little-endian word, zero above them, from the aligned 8-byte words
-// that hold them (an aligned word that holds one byte of a buffer lies inside the buffer's pages).
-__device__ __forceinline__ uint64_t load_le_bytes(const uint8_t* p, uint32_t nb) {
-  const uintptr_t addr = (uintptr_t)p;
-  const uint64_t* w = (const uint64_t*)(addr & ~(uintptr_t)7);
-  const uint32_t sh = (uint32_t)(addr & 7);
-  uint64_t v = w[0] >> (8 * sh);
-  if (sh && sh + nb > 8) v |= w[1] << (64 - 8 * sh);
-  return nb >= 8 ? v : (v & ((1ULL << (8 * nb)) - 1));
-}
-
 // Byte string -> (hi, lo): two chains over little-endian 8-byte words (the last one zero-padded),
-// finished with the length.
+// finished with the length.  The string is read through the aligned words that hold it, each once and
+// one word ahead of the mixing (an aligned word that holds one byte of a buffer lies inside the
+// buffer's pages); consecutive ones are funnelled by the string's byte offset.  The loads are global
+// ones (the pointer is moved, not rebuilt from an integer, which would make them flat).
 __device__ __forceinline__ void hash_key_str(const uint8_t* s, uint64_t len, uint64_t seed, uint64_t& hi,
                                              uint64_t& lo) {
   uint64_t a = seed, b = seed ^ kSqrt2;
+  const uint32_t off = (uint32_t)((uintptr_t)s & 7), sh = 8 * off;
+  const uint64_t* w = (const uint64_t*)(s - off);
+  const uint64_t end = off + len;  // bytes of the aligned words up to the string's end
+  uint64_t c0 = len ? w[0] : 0, c1 = end > 8 ? w[1] : 0;
   for (uint64_t i = 0; i < len; i += 8) {
-    const uint64_t w = load_le_bytes(s + i, (uint32_t)min<uint64_t>(8, len - i));
-    a = mix_a(a ^ w);
-    b = mix_b(b ^ w);
+    const uint64_t c2 = end > i + 16 ? w[i / 8 + 2] : 0;
+    uint64_t v = (c0 >> sh) | (c1 << 1 << (63 - sh));
+    if (len - i < 8) v &= (1ULL << (8 * (uint32_t)(len - i))) - 1;
+    a = mix_a(a ^ v);
+    b = mix_b(b ^ v);
+    c0 = c1;
+    c1 = c2;
   }
   hi = mix_a(a ^ len);
   lo = mix_b(b ^ len);
