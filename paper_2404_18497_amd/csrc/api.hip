@@ -253,9 +253,15 @@ static uint64_t host_bits(const uint64_t* w, uint64_t pos, uint32_t width) {
 
 static uint32_t host_bit_length(uint64_t v) { return v ? 64 - __builtin_clzll(v) : 0; }
 
-// Checks that an image is internally consistent, so the query kernel never reads outside it.
-static phobic_status check_image(const uint64_t* w, uint64_t nwords) {
-  auto bad = [](const char* what) { return fail(PHOBIC_E_FORMAT, std::string("malformed image: ") + what); };
+// Checks that an image is internally consistent, so the query kernel never reads outside it: its header
+// and section extents (check_header), then everything in the sections, on the host (check_sections) or,
+// for the uploaded image, on the device (k_check_sections).
+static phobic_status bad_image(const char* what) {
+  return fail(PHOBIC_E_FORMAT, std::string("malformed image: ") + what);
+}
+
+static phobic_status check_header(const uint64_t* w, uint64_t nwords) {
+  auto bad = bad_image;
   if (nwords < kHeaderWords || w[kHMagic] != kMagic) return bad("magic");
   if (w[kHWords] != nwords) return bad("length");
   const uint64_t n = w[kHN], K = w[kHK], B = w[kHB], total = w[kHTotal];
@@ -277,6 +283,15 @@ static phobic_status check_image(const uint64_t* w, uint64_t nwords) {
   if (se != so + ((K + 1) * w[kHWoff] + 63) / 64 + 1 || sd != se + B + 1 || su < sd || ss < su || sr < ss ||
       sr > nwords)
     return bad("section layout");
+  return PHOBIC_OK;
+}
+
+static phobic_status check_sections(const uint64_t* w, uint64_t nwords) {
+  auto bad = bad_image;
+  const uint64_t n = w[kHN], K = w[kHK], B = w[kHB], total = w[kHTotal], c = w[kHNcompact];
+  const uint64_t coding = w[kHCoding] & 0xFF;
+  const uint64_t so = w[kHSecOff], se = w[kHSecEnc], sd = w[kHSecData], su = w[kHSecUnary], ss = w[kHSecSel],
+                 sr = w[kHSecRemap];
   // offsets: 0 first, total last, non-decreasing
   uint64_t prev = 0;
   for (uint64_t j = 0; j <= K; j++) {
@@ -345,6 +360,98 @@ static phobic_status check_image(const uint64_t* w, uint64_t nwords) {
   return PHOBIC_OK;
 }
 
+// The same checks on the device.  The select entries are checked segment by segment: entry s names a set
+// bit with exactly kSelBlock ones from there to the next entry's (the last one: the remaining ones to the
+// end), and none precede entry 0's, so by induction every entry names the one it should; the three
+// distances follow from the ones after it.  Bound: one pass over the image (0.25 B per key).
+enum : uint32_t { kBadOffsets, kBadEncoders, kBadUnary, kBadSelect, kBadRemap };
+
+__global__ __launch_bounds__(256) void k_check_clear(uint32_t* flag) {
+  if (threadIdx.x == 0) *flag = 0;
+}
+
+__global__ __launch_bounds__(256) void k_check_sections(const uint64_t* __restrict__ w, uint32_t* __restrict__ flag) {
+  const uint64_t tid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x, nt = (uint64_t)gridDim.x * blockDim.x;
+  const uint64_t n = w[kHN], K = w[kHK], B = w[kHB], total = w[kHTotal], R = w[kHR], dmin = w[kHDmin];
+  const uint64_t sd = w[kHSecData], su = w[kHSecUnary];
+  const uint32_t woff = (uint32_t)w[kHWoff];
+  uint32_t bad = 0;
+  for (uint64_t j = tid; j <= K; j += nt) {
+    const uint64_t* off = w + w[kHSecOff];
+    const uint64_t o = expected_offset(j, R) + dmin + get_bits(off, j * woff, woff);
+    if (j == 0 ? o != 0 : o < expected_offset(j - 1, R) + dmin + get_bits(off, (j - 1) * woff, woff)) bad |= 1u << kBadOffsets;
+    if (j == K && o != total) bad |= 1u << kBadOffsets;
+  }
+  const uint64_t data_bits = (su - sd - 1) * 64;
+  for (uint64_t i = tid; i < B; i += nt) {
+    const uint64_t e = w[w[kHSecEnc] + i];
+    const uint32_t wd = (uint32_t)(e & 0xFF);
+    if (wd > 32 || (e >> 8) + (uint64_t)wd * K > data_bits) bad |= 1u << kBadEncoders;
+  }
+  if ((w[kHCoding] & 0xFF) == PHOBIC_IC_RICE) {
+    const uint64_t nvals = K * (B - w[kHNcompact]), nsel = (nvals + kSelBlock - 1) / kSelBlock;
+    const uint64_t* un = w + su;
+    const uint64_t* sel = w + w[kHSecSel];
+    const uint64_t U = (w[kHUbits] + 63) / 64, ubits = U * 64;
+    if (tid == 0 && un[U] != 0) bad |= 1u << kBadUnary;
+    if (nsel == 0)
+      for (uint64_t x = tid; x < U; x += nt)
+        if (un[x]) bad |= 1u << kBadUnary;
+    for (uint64_t s = tid; s < nsel; s += nt) {
+      const uint64_t entry = sel[s], a = entry & 0xFFFFFFFFULL;
+      const uint64_t end = s + 1 < nsel ? sel[s + 1] & 0xFFFFFFFFULL : ubits;
+      const uint64_t want = s + 1 < nsel ? kSelBlock : nvals - s * kSelBlock;
+      if (a >= ubits || end <= a || end > ubits || !((un[a >> 6] >> (a & 63)) & 1)) {
+        bad |= 1u << kBadSelect;
+        continue;
+      }
+      if (s == 0) {
+        uint64_t before = un[a >> 6] & ((1ULL << (a & 63)) - 1);
+        for (uint64_t x = 0; x < a >> 6; x++) before |= un[x];
+        if (before) bad |= 1u << kBadSelect;
+      }
+      uint64_t word = a >> 6, x = un[word] & (~0ULL << (a & 63)), seen = 0, out = a;
+      uint32_t k = 1;  // the next distance: one number kSelSub k from the entry's on
+      for (;; x = un[++word]) {
+        const bool last = word == (end - 1) >> 6;
+        if (last && (end & 63)) x &= (1ULL << (end & 63)) - 1;
+        const uint32_t c = __popcll(x);
+        for (; k < kSelBlock / kSelSub && k * kSelSub < want && seen + c > k * kSelSub; k++) {
+          const uint64_t rel = word * 64 + select_in_word(x, (uint32_t)(k * kSelSub - seen)) - a;
+          out |= (rel < kSelRelNone ? rel : kSelRelNone) << (32 + 10 * (k - 1));
+        }
+        seen += c;
+        if (last) break;
+      }
+      if (seen != want) bad |= 1u << kBadUnary;
+      if (out != entry) bad |= 1u << kBadSelect;
+    }
+  }
+  const uint64_t nremap = total - n;
+  const uint32_t wr = (uint32_t)w[kHWremap];
+  for (uint64_t g = tid; g < nremap; g += nt)
+    if (get_bits(w + w[kHSecRemap], g * wr, wr) >= n) bad |= 1u << kBadRemap;
+  if (bad) atomicOr(flag, bad);
+}
+
+// Images of fewer words are checked on the host: up to about here it takes less time than the round
+// trip to the device's answer.
+constexpr uint64_t kDeviceCheckWords = 1 << 14;
+
+// Whether the sections of a checked header lie inside the image, each with its pad word, in arithmetic
+// that cannot wrap: what the device check reads.  (The host check refuses what does not fit.)
+static bool sections_fit(const uint64_t* w, uint64_t nwords) {
+  const uint64_t K = w[kHK], B = w[kHB], nremap = w[kHTotal] - w[kHN];
+  const uint64_t su = w[kHSecUnary], ss = w[kHSecSel], sr = w[kHSecRemap], bits = nwords * 64;
+  if (K >> 31 || w[kHUbits] > bits || (K + 1) * w[kHWoff] > bits || su <= w[kHSecData]) return false;
+  if (w[kHNremap] != nremap || (nremap && w[kHWremap] != host_bit_length(w[kHN] ? w[kHN] - 1 : 0))) return false;
+  if (nremap && (w[kHWremap] == 0 || nremap > bits / w[kHWremap])) return false;
+  if (sr + (nremap ? (nremap * w[kHWremap] + 63) / 64 + 1 : 0) != nwords) return false;
+  if ((w[kHCoding] & 0xFF) != PHOBIC_IC_RICE) return su == ss && ss == sr;
+  return su + (w[kHUbits] + 63) / 64 + 1 == ss &&
+         ss + (K * (B - w[kHNcompact]) + kSelBlock - 1) / kSelBlock + 1 == sr;
+}
+
 }  // namespace phobic
 
 using namespace phobic;
@@ -402,17 +509,26 @@ extern "C" phobic_status phobic_deserialize(const void* h_buf, uint64_t bytes, v
   *out = nullptr;
   if (!h_buf || bytes % 8 != 0) return fail(PHOBIC_E_FORMAT, "image size is not a whole number of words");
   const uint64_t nwords = bytes / 8;
-  std::vector<uint64_t> w(nwords);
-  std::memcpy(w.data(), h_buf, bytes);
-  phobic_status s = check_image(w.data(), nwords);
+  if (nwords < kHeaderWords) return bad_image("length");
+  uint64_t w[kHeaderWords];  // the header; the sections stay in h_buf
+  std::memcpy(w, h_buf, sizeof(w));
+  phobic_status s = check_header(w, nwords);
   if (s != PHOBIC_OK) return s;
+  const bool on_device = nwords >= kDeviceCheckWords && sections_fit(w, nwords);
+  std::vector<uint64_t> copy;
+  if (!on_device) {
+    copy.resize(nwords);
+    std::memcpy(copy.data(), h_buf, bytes);
+    s = check_sections(copy.data(), nwords);
+    if (s != PHOBIC_OK) return s;
+  }
   hipStream_t st = (hipStream_t)hip_stream;
   auto h = new phobic_mphf();
   PHOBIC_HIP(hipGetDevice(&h->device));
   h->n = w[kHN];
   h->K = w[kHK];
   h->B = (uint32_t)w[kHB];
-  h->header.assign(w.begin(), w.begin() + kHeaderWords);
+  h->header.assign(w, w + kHeaderWords);
   phobic_params_default(&h->prm);
   h->prm.partition_size = (uint32_t)w[kHP];
   std::memcpy(&h->prm.lambda, &w[kHLambda], 8);
@@ -428,12 +544,26 @@ extern "C" phobic_status phobic_deserialize(const void* h_buf, uint64_t bytes, v
     phobic_free(h);
     return r;
   }
-  hipError_t e = pool_alloc((void**)&h->d_image, bytes, st);
-  if (e == hipSuccess) e = hipMemcpyAsync(h->d_image, w.data(), bytes, hipMemcpyHostToDevice, st);
+  hipError_t e = pool_alloc((void**)&h->d_image, bytes + sizeof(uint64_t), st);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(h->d_image, on_device ? h_buf : copy.data(), bytes, hipMemcpyHostToDevice, st);
+  uint32_t flag = 0;
+  if (on_device && e == hipSuccess) {
+    uint32_t* d_flag = (uint32_t*)(h->d_image + nwords);
+    hipLaunchKernelGGL(k_check_clear, dim3(1), dim3(64), 0, st, d_flag);
+    hipLaunchKernelGGL(k_check_sections, dim3(1024), dim3(256), 0, st, h->d_image, d_flag);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipMemcpyAsync(&flag, d_flag, sizeof(flag), hipMemcpyDeviceToHost, st);
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(st);
   if (e != hipSuccess) {
     phobic_free(h);
     return fail(e == hipErrorOutOfMemory ? PHOBIC_E_OOM : PHOBIC_E_DEVICE, hipGetErrorString(e));
+  }
+  if (flag) {
+    static const char* const what[] = {"offsets", "encoder table", "unary stream", "select samples", "remap entries"};
+    phobic_free(h);
+    return bad_image(what[__builtin_ctz(flag)]);
   }
   fill_query_args(h);
   *out = h;
