@@ -1,5 +1,5 @@
 """Image checks on load, on both sides of the size from which the sections are checked on the device
-(2^14 words): single flipped bits all over an image are accepted or refused exactly as a plain numpy
+(2^13 words): single flipped bits all over an image are accepted or refused exactly as a plain numpy
 reading of the format says, for minimal, non-minimal, Compact and mixed images."""
 
 import numpy as np
@@ -54,7 +54,7 @@ def test_flipped_bits(n, kw):
     keys = torch.from_numpy(synth.u64_keys(n, 5).view(np.int64)).cuda()
     h = binding.build_u64(keys, binding.params(lam=7.0, **kw))
     img = h.serialize()
-    assert (img.size < 1 << 14) == (n == 20_000)
+    assert (img.size < 1 << 13) == (n == 20_000)
     rng = np.random.default_rng(n)
     secs = [int(x) for x in img[12:18]] + [img.size]
     words = [rng.integers(a, b, 3) for a, b in zip(secs, secs[1:]) if b > a]
