@@ -331,49 +331,135 @@ __global__ __launch_bounds__(kBlock) void k_bucket_sort(const ulonglong2* __rest
 }
 
 // ---------------------------------------------------------------------------------------------
-// Bucket mapping and ordering for wide partitions (more keys or buckets than one workgroup holds
-// in LDS), one workgroup of kWideThreads per partition.  The per-bucket counts, then start
-// offsets, live in a global row cnt[j B .. j B + B) (zero on entry) and every key's rank inside its
-// bucket in rank[]; only the sort keys (size << 16 | bucket) of the nbpad buckets are in LDS.
-// Keys of one partition are read twice (bucket and rank, then the scatter) and their buckets
-// computed twice.  A bucket of 65536 or more keys sets the capacity bit.
+// Bucket mapping and ordering for wide partitions (more keys or buckets than k_bucket_sort holds in
+// LDS), one workgroup of kWideThreads per partition.  The bucket counts are LDS counters, whose place
+// the sort keys (size << 16 | bucket) then take; every key's bucket and rank wait in rec[] between the two
+// passes over the keys.  The start offsets are in LDS too when they fit (kLdsStarts: B up to 16384),
+// else in the global row starts[j B .. j B + B).  A bucket of 65536 or more keys sets the capacity bit.
+//
+// Bound: latency (one workgroup per CU), so both passes keep kWideBatch items per thread in flight, and
+// the sort leaves LDS only where elements 512 or more apart meet (14 barriers for 8192 buckets in
+// place of 91).  With global counters, one item at a time and a bitonic sort through LDS alone, 200
+// partitions of 50 000 keys took 1011 us; this way 300 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int kWideThreads = 1024;
+constexpr int kWideBatch = 4;
+constexpr uint32_t kWideLdsStarts = 16384;
 
-__device__ __forceinline__ uint32_t load_l2_u32(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Descending bitonic sort of keys[0, n) (n a power of two; entries beyond are zero) by one wavefront
+// in registers: element i = lane * E + r; sub-stages with distance below E stay inside a lane, the
+// others exchange with lane ^ (distance / E).  No workgroup barrier.
+template <int E>
+__device__ __forceinline__ void bitonic_stage(uint32_t (&v)[E], uint32_t k, uint32_t j0, uint32_t lane) {
+#pragma unroll
+  for (uint32_t j = j0; j > 0; j >>= 1) {
+    if (j >= (uint32_t)E) {
+      const uint32_t jl = j / E;
+      const bool lower = (lane & jl) == 0;
+#pragma unroll
+      for (int r = 0; r < E; r++) {
+        const bool desc = ((lane * E + r) & k) == 0;
+        const uint32_t pv = __shfl_xor(v[r], (int)jl);
+        v[r] = (lower == desc) ? max(v[r], pv) : min(v[r], pv);
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < E; r++) {
+        if ((r & j) == 0) {
+          const bool desc = ((lane * E + r) & k) == 0;
+          const uint32_t a = v[r], b = v[r ^ j];
+          v[r] = desc ? max(a, b) : min(a, b);
+          v[r ^ j] = desc ? min(a, b) : max(a, b);
+        }
+      }
+    }
+  }
 }
 
-__global__ __launch_bounds__(kWideThreads) void k_bucket_sort_wide(const ulonglong2* __restrict__ codes,
-                                                                   const uint64_t* __restrict__ off,
-                                                                   const uint64_t* __restrict__ T, uint32_t B,
-                                                                   uint32_t nbpad, uint32_t* __restrict__ cnt,
-                                                                   uint32_t* __restrict__ rank,
-                                                                   uint64_t* __restrict__ sortedf,
-                                                                   uint32_t* __restrict__ blist,
-                                                                   uint32_t* __restrict__ nbk, uint32_t* __restrict__ info) {
+template <int E>
+__device__ __forceinline__ void wave_bitonic_desc(uint32_t* keys, uint32_t n, uint32_t lane) {
+  constexpr uint32_t N = 64 * E;
+  uint32_t v[E];
+#pragma unroll
+  for (int r = 0; r < E; r++) {
+    const uint32_t i = lane * E + r;
+    v[r] = i < n ? keys[i] : 0u;
+  }
+#pragma unroll
+  for (uint32_t k = 2; k <= N; k <<= 1) bitonic_stage<E>(v, k, k >> 1, lane);
+#pragma unroll
+  for (int r = 0; r < E; r++) {
+    const uint32_t i = lane * E + r;
+    if (i < n) keys[i] = v[r];
+  }
+}
+
+// nbpad <= 512 (at most 8 keys per lane, so the registers do not limit the kernel's occupancy)
+__device__ __forceinline__ void wave_sort_keys(uint32_t* keys, uint32_t nbpad, uint32_t lane) {
+  if (nbpad <= 64) wave_bitonic_desc<1>(keys, nbpad, lane);
+  else if (nbpad == 128) wave_bitonic_desc<2>(keys, nbpad, lane);
+  else if (nbpad == 256) wave_bitonic_desc<4>(keys, nbpad, lane);
+  else wave_bitonic_desc<8>(keys, nbpad, lane);
+}
+
+// 512 consecutive keys by one wavefront: sorted (kSort), or merged from a bitonic sequence; descending,
+// or ascending (by the complements).
+template <bool kSort>
+__device__ __forceinline__ void wave_sort_512(uint32_t* keys, bool desc, uint32_t lane) {
+  constexpr int E = 8;
+  const uint32_t flip = desc ? 0u : ~0u;
+  uint32_t v[E];
+#pragma unroll
+  for (int r = 0; r < E; r++) v[r] = keys[lane * E + r] ^ flip;
+  if (kSort) {
+#pragma unroll
+    for (uint32_t k = 2; k <= 64 * E; k <<= 1) bitonic_stage<E>(v, k, k >> 1, lane);
+  } else {
+    bitonic_stage<E>(v, 64 * E, 32 * E, lane);
+  }
+#pragma unroll
+  for (int r = 0; r < E; r++) keys[lane * E + r] = v[r] ^ flip;
+}
+
+template <bool kLdsStarts>
+__global__ __launch_bounds__(kWideThreads) void k_bucket_sort_wide(
+    const ulonglong2* __restrict__ codes, const uint64_t* __restrict__ off, const uint64_t* __restrict__ T, uint32_t B,
+    uint32_t nbpad, uint32_t* __restrict__ starts, uint32_t* __restrict__ rec, uint64_t* __restrict__ sortedf,
+    uint32_t* __restrict__ blist, uint32_t* __restrict__ nbk, uint32_t* __restrict__ info) {
   extern __shared__ __align__(16) uint32_t lds[];
-  uint32_t* key = lds;  // [nbpad]
-  __shared__ uint32_t part[kWideThreads];
+  uint32_t* key = lds;  // [nbpad]: counts, then sort keys
+  __shared__ uint64_t Ts[kTableIntervals + 1];
+  __shared__ uint32_t part[kWideThreads / 64];
   __shared__ uint32_t nonempty, toolarge;
-  const uint32_t tid = threadIdx.x;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t j = blockIdx.x;
   const uint64_t base = off[j];
   const uint32_t nj = (uint32_t)(off[j + 1] - base);
-  uint32_t* row = cnt + j * B;
+  uint32_t* row = kLdsStarts ? lds + nbpad : starts + j * B;
   if (tid == 0) {
     nonempty = 0;
     toolarge = 0;
   }
-  for (uint32_t i = tid; i < nj; i += kWideThreads) {
-    const uint32_t b = bucket_of(codes[base + i].y, T, B);
-    rank[base + i] = atomicAdd(&row[b], 1u);
+  for (uint32_t x = tid; x < nbpad; x += kWideThreads) key[x] = 0;
+  for (uint32_t x = tid; x <= kTableIntervals; x += kWideThreads) Ts[x] = T[x];
+  __syncthreads();
+  for (uint32_t i0 = tid; i0 < nj; i0 += kWideBatch * kWideThreads) {
+    uint64_t lo[kWideBatch];
+#pragma unroll
+    for (int u = 0; u < kWideBatch; u++) lo[u] = codes[base + min(i0 + (uint32_t)u * kWideThreads, nj - 1)].y;
+#pragma unroll
+    for (int u = 0; u < kWideBatch; u++) {
+      const uint32_t i = i0 + (uint32_t)u * kWideThreads;
+      if (i < nj) {
+        const uint32_t b = bucket_of(lo[u], Ts, B);
+        rec[base + i] = (b << 16) | (atomicAdd(&key[b], 1u) & 0xFFFFu);
+      }
+    }
   }
-  __threadfence();
   __syncthreads();
   uint32_t ne = 0, big = 0;
   for (uint32_t x = tid; x < nbpad; x += kWideThreads) {
-    const uint32_t c = x < B ? load_l2_u32(&row[x]) : 0u;
+    const uint32_t c = key[x];
     big |= c > 0xFFFFu;
     key[x] = c ? ((min(c, 0xFFFFu) << 16) | x) : 0u;
     ne += c != 0;
@@ -386,18 +472,27 @@ __global__ __launch_bounds__(kWideThreads) void k_bucket_sort_wide(const ulonglo
     return;
   }
   // bitonic sort of key[] into descending order: size first, then bucket index
-  for (uint32_t k = 2; k <= nbpad; k <<= 1) {
-    for (uint32_t sd = k >> 1; sd > 0; sd >>= 1) {
-      for (uint32_t x = tid; x < nbpad; x += kWideThreads) {
-        const uint32_t y = x ^ sd;
-        if (y > x) {
+  if (nbpad <= 512) {
+    if (wave == 0) wave_sort_keys(key, nbpad, lane);
+    __syncthreads();
+  } else {
+    for (uint32_t x = wave * 512; x < nbpad; x += kWideThreads / 64 * 512)
+      wave_sort_512<true>(key + x, (x & 512) == 0, lane);
+    __syncthreads();
+    for (uint32_t k = 1024; k <= nbpad; k <<= 1) {
+      for (uint32_t sd = k >> 1; sd >= 512; sd >>= 1) {
+        for (uint32_t q = tid; q < nbpad / 2; q += kWideThreads) {  // pair q: x has bit sd clear
+          const uint32_t x = ((q & ~(sd - 1)) << 1) | (q & (sd - 1)), y = x | sd;
           const uint32_t a = key[x], b = key[y];
           if ((x & k) == 0 ? (a < b) : (a > b)) {
             key[x] = b;
             key[y] = a;
           }
         }
+        __syncthreads();
       }
+      for (uint32_t x = wave * 512; x < nbpad; x += kWideThreads / 64 * 512)
+        wave_sort_512<false>(key + x, (x & k) == 0, lane);
       __syncthreads();
     }
   }
@@ -406,15 +501,16 @@ __global__ __launch_bounds__(kWideThreads) void k_bucket_sort_wide(const ulonglo
   const uint32_t x0 = min(nbpad, tid * ipt), x1 = min(nbpad, x0 + ipt);
   uint32_t local = 0;
   for (uint32_t x = x0; x < x1; x++) local += key[x] >> 16;
-  part[tid] = local;
-  __syncthreads();
-  for (uint32_t d = 1; d < kWideThreads; d <<= 1) {
-    const uint32_t v = tid >= d ? part[tid - d] : 0;
-    __syncthreads();
-    part[tid] += v;
-    __syncthreads();
+  uint32_t inc = local;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t y = __shfl_up(inc, d);
+    if (lane >= (uint32_t)d) inc += y;
   }
-  uint32_t run = part[tid] - local;
+  if (lane == 63) part[wave] = inc;
+  __syncthreads();
+  uint32_t run = inc - local;
+  for (uint32_t w = 0; w < wave; w++) run += part[w];
   const uint32_t nb = nonempty;
   for (uint32_t x = x0; x < x1; x++) {
     const uint32_t kx = key[x];
@@ -428,15 +524,22 @@ __global__ __launch_bounds__(kWideThreads) void k_bucket_sort_wide(const ulonglo
     nbk[j] = nb;
     if (nb) atomicMax(&info[1], key[0] >> 16);
   }
-  __threadfence();
   __syncthreads();
-  for (uint32_t i = tid; i < nj; i += kWideThreads) {
-    const ulonglong2 c = codes[base + i];
-    const uint32_t b = bucket_of(c.y, T, B);
-    sortedf[base + load_l2_u32(&row[b]) + rank[base + i]] = fingerprint(c.x, c.y);
+  for (uint32_t i0 = tid; i0 < nj; i0 += kWideBatch * kWideThreads) {
+    ulonglong2 c[kWideBatch];
+    uint32_t r[kWideBatch];
+#pragma unroll
+    for (int u = 0; u < kWideBatch; u++) {
+      const uint64_t i = base + min(i0 + (uint32_t)u * kWideThreads, nj - 1);
+      c[u] = codes[i];
+      r[u] = rec[i];
+    }
+#pragma unroll
+    for (int u = 0; u < kWideBatch; u++)
+      if (i0 + (uint32_t)u * kWideThreads < nj)
+        sortedf[base + row[r[u] >> 16] + (r[u] & 0xFFFF)] = fingerprint(c[u].x, c[u].y);
   }
 }
-
 
 // ---------------------------------------------------------------------------------------------
 // Hash, partition, bucket and order, main path: coarse bins of G = 2^gshift consecutive partitions,
@@ -790,59 +893,6 @@ __global__ __launch_bounds__(kSplitThreads) __attribute__((amdgpu_waves_per_eu(8
   const uint32_t mask = nb - 1;
   split_range<E, false>(
       in, a, b, nb, start, [=](const E& v) { return SplitElem<E>::bin(v, seed, K, gshift) & mask; }, L, out);
-}
-
-// Descending bitonic sort of keys[0, n) (n a power of two; entries beyond are zero) by one wavefront
-// in registers: element i = lane * E + r; sub-stages with distance below E stay inside a lane, the
-// others exchange with lane ^ (distance / E).  No workgroup barrier.
-template <int E>
-__device__ __forceinline__ void wave_bitonic_desc(uint32_t* keys, uint32_t n, uint32_t lane) {
-  constexpr uint32_t N = 64 * E;
-  uint32_t v[E];
-#pragma unroll
-  for (int r = 0; r < E; r++) {
-    const uint32_t i = lane * E + r;
-    v[r] = i < n ? keys[i] : 0u;
-  }
-#pragma unroll
-  for (uint32_t k = 2; k <= N; k <<= 1) {
-#pragma unroll
-    for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-      if (j >= (uint32_t)E) {
-        const uint32_t jl = j / E;
-        const bool lower = (lane & jl) == 0;
-#pragma unroll
-        for (int r = 0; r < E; r++) {
-          const bool desc = ((lane * E + r) & k) == 0;
-          const uint32_t pv = __shfl_xor(v[r], (int)jl);
-          v[r] = (lower == desc) ? max(v[r], pv) : min(v[r], pv);
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < E; r++) {
-          if ((r & j) == 0) {
-            const bool desc = ((lane * E + r) & k) == 0;
-            const uint32_t a = v[r], b = v[r ^ j];
-            v[r] = desc ? max(a, b) : min(a, b);
-            v[r ^ j] = desc ? min(a, b) : max(a, b);
-          }
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < E; r++) {
-    const uint32_t i = lane * E + r;
-    if (i < n) keys[i] = v[r];
-  }
-}
-
-// nbpad <= 512 (at most 8 keys per lane, so the registers do not limit the kernel's occupancy)
-__device__ __forceinline__ void wave_sort_keys(uint32_t* keys, uint32_t nbpad, uint32_t lane) {
-  if (nbpad <= 64) wave_bitonic_desc<1>(keys, nbpad, lane);
-  else if (nbpad == 128) wave_bitonic_desc<2>(keys, nbpad, lane);
-  else if (nbpad == 256) wave_bitonic_desc<4>(keys, nbpad, lane);
-  else wave_bitonic_desc<8>(keys, nbpad, lane);
 }
 
 // One workgroup per coarse bin of up to kMaxG partitions.  info[0] |= error bits, info[1] = max
@@ -1999,16 +2049,18 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
     if (part_codes_out)
       PHOBIC_HIP(hipMemcpyAsync(part_codes_out, codes, n * sizeof(ulonglong2), hipMemcpyDeviceToDevice, st));
     if (wide) {
-      const size_t sort_lds = (size_t)nbpad * sizeof(uint32_t);
-      if (sort_lds > max_lds_per_group())
+      const bool lds_starts = B <= kWideLdsStarts;
+      const size_t sort_lds = ((size_t)nbpad + (lds_starts ? B : 0)) * sizeof(uint32_t);
+      const size_t static_lds = (kTableIntervals + 1) * sizeof(uint64_t) + 256;
+      if (sort_lds + static_lds > max_lds_per_group())
         return fail(PHOBIC_E_CAPACITY, "B = " + std::to_string(B) + " buckets do not fit the LDS of one workgroup");
-      uint32_t *wcnt, *wrank;
-      PHOBIC_HIP(S.get(&wcnt, K * B));
-      PHOBIC_HIP(S.get(&wrank, n));
-      hipLaunchKernelGGL(k_fill_u32, dim3(grid_for(K * B)), dim3(kBlock), 0, st, wcnt, K * B, 0u);
-      PHOBIC_HIP(allow_lds(k_bucket_sort_wide, sort_lds));
-      hipLaunchKernelGGL(k_bucket_sort_wide, dim3((uint32_t)K), dim3(kWideThreads), sort_lds, st, codes, off,
-                         h->d_table, B, nbpad, wcnt, wrank, sortedf, blist, nbk, err);
+      uint32_t *wstarts = nullptr, *wrec;
+      if (!lds_starts) PHOBIC_HIP(S.get(&wstarts, K * B));
+      PHOBIC_HIP(S.get(&wrec, n));
+      auto kernel = lds_starts ? k_bucket_sort_wide<true> : k_bucket_sort_wide<false>;
+      PHOBIC_HIP(allow_lds(kernel, sort_lds));
+      hipLaunchKernelGGL(kernel, dim3((uint32_t)K), dim3(kWideThreads), sort_lds, st, codes, off, h->d_table, B, nbpad,
+                         wstarts, wrec, sortedf, blist, nbk, err);
     } else {
       const size_t sort_lds = (2 * (size_t)nbpad + std::max<uint64_t>(old_info[0], 1)) * sizeof(uint32_t);
       hipLaunchKernelGGL(k_bucket_sort, dim3((uint32_t)K), dim3(kBlock), sort_lds, st, codes, off, h->d_table, B,
