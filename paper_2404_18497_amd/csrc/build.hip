@@ -43,12 +43,13 @@ __global__ void k_fill_u32(uint32_t* __restrict__ p, uint64_t n, uint32_t v) {
 }
 
 // The start of a build in one launch: error words (4) and info words (8) cleared, and the n counters at
-// cnt.
+// cnt.  one_bin (else null): the bounds 0, nkeys of a single coarse bin.
 __global__ void k_build_clear(uint32_t* __restrict__ err, uint64_t* __restrict__ d64, uint32_t* __restrict__ cnt,
-                              uint64_t n) {
+                              uint64_t n, uint64_t* __restrict__ one_bin, uint64_t nkeys) {
   const uint64_t i0 = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
   if (i0 < 4) err[i0] = 0;
   if (i0 < 8) d64[i0] = 0;
+  if (one_bin && i0 < 2) one_bin[i0] = i0 ? nkeys : 0;
   for (uint64_t i = i0; i < n; i += (uint64_t)gridDim.x * blockDim.x) cnt[i] = 0;
 }
 
@@ -72,11 +73,19 @@ __global__ void k_image_init(uint64_t* __restrict__ img, uint64_t nw, const uint
 }
 
 // out[c][r] = in[r][c] for an R x Cn array of u32, in 64 x 64 tiles staged through LDS so that both
-// the reads (along a row of `in`) and the writes (along a row of `out`) are contiguous.
+// the reads (along a row of `in`) and the writes (along a row of `out`) are contiguous.  The launch also
+// clears the statistics block of nst words that the next kernel adds to, with the offset residue range
+// at word mm_at set to (LLONG_MAX, LLONG_MIN), the identities of minimum and maximum.
 constexpr uint32_t kTile = 64;
 __global__ __launch_bounds__(kTile * kTile / 16) void k_transpose_u32(const uint32_t* __restrict__ in, uint64_t R,
-                                                                      uint64_t Cn, uint32_t* __restrict__ out) {
+                                                                      uint64_t Cn, uint32_t* __restrict__ out,
+                                                                      uint64_t* __restrict__ stats, uint64_t nst,
+                                                                      uint64_t mm_at) {
   __shared__ uint32_t tile[kTile][kTile + 1];
+  constexpr uint32_t kThreads = kTile * kTile / 16;
+  for (uint64_t i = (uint64_t)blockIdx.x * kThreads + threadIdx.y * kTile + threadIdx.x; i < nst;
+       i += (uint64_t)gridDim.x * kThreads)
+    stats[i] = i == mm_at ? (uint64_t)LLONG_MAX : (i == mm_at + 1 ? (uint64_t)LLONG_MIN : 0);
   const uint64_t tr = (R + kTile - 1) / kTile, tc = (Cn + kTile - 1) / kTile;
   for (uint64_t t = blockIdx.x; t < tr * tc; t += gridDim.x) {
     const uint64_t r0 = (t / tc) * kTile, c0 = (t % tc) * kTile;
@@ -1168,16 +1177,51 @@ constexpr uint32_t kPackChunk = kPackThreads * kPackItems;
 // per thread) and its 16-bit count fields (at most kPackChunk) cannot overflow.
 static_assert(kPackChunk / kBlock <= 255 && kPackChunk < 65536, "count fields of k_encoder_stats");
 
-// Workgroup (c, i) reads chunk c of encoder i (j in [c kPackChunk, (c + 1) kPackChunk), gridDim.x
+// Offset residues delta_j = toff[j] - E_j: minimum and maximum over j in [0, K] (gridDim.x workgroups).
+__device__ __forceinline__ void offset_stats(const uint64_t* __restrict__ toff, uint64_t K, uint64_t R,
+                                             long long* __restrict__ mm) {
+  long long lmin = LLONG_MAX, lmax = LLONG_MIN;
+  for (uint64_t jj = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; jj <= K; jj += (uint64_t)gridDim.x * blockDim.x) {
+    long long d = (long long)(toff[jj] - expected_offset(jj, R));
+    lmin = min(lmin, d);
+    lmax = max(lmax, d);
+  }
+  __shared__ long long wmin[kBlock / 64], wmax[kBlock / 64];
+  for (int o = 32; o > 0; o >>= 1) {
+    lmin = min(lmin, (long long)__shfl_xor(lmin, o));
+    lmax = max(lmax, (long long)__shfl_xor(lmax, o));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    wmin[threadIdx.x >> 6] = lmin;
+    wmax[threadIdx.x >> 6] = lmax;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {  // one pair of atomics per workgroup
+    for (int w = 1; w < kBlock / 64; w++) {
+      lmin = min(lmin, wmin[w]);
+      lmax = max(lmax, wmax[w]);
+    }
+    atomicMin(&mm[0], lmin);
+    atomicMax(&mm[1], lmax);
+  }
+}
+
+// Workgroup (c, i), i < B (the row i = B takes the offset residues), reads chunk c of encoder i (j in [c kPackChunk, (c + 1) kPackChunk), gridDim.x
 // chunks): shsum[i * 33 + b] += sum_j (v_ij >> b), vmax[i] = max(vmax[i], max_j v_ij) (both start
-// at zero, k_stats_init), and the chunk's bit counts c_k = #{j : bit k of v_ij is set} go to
+// at zero, k_transpose_u32), and the chunk's bit counts c_k = #{j : bit k of v_ij is set} go to
 // ccnt[(i gridDim.x + c) 32 + k].  Since v >> b = sum_{k >= b} bit_k(v) 2^(k - b), the counts give
 // sum_j (v_ij >> b) = sum_{k >= b} c_k 2^(k - b) exactly, for any b, here and once the Rice
 // parameters are known (k_chunk_carry).  A thread counts eight bits per add: byte t of cnt8[s]
 // counts bit 8 t + s of its values.
 __global__ __launch_bounds__(kBlock) void k_encoder_stats(const uint32_t* __restrict__ pilots, uint64_t K,
                                                           uint64_t* __restrict__ shsum, uint32_t* __restrict__ vmax,
-                                                          uint32_t* __restrict__ ccnt) {
+                                                          uint32_t* __restrict__ ccnt, uint32_t B,
+                                                          const uint64_t* __restrict__ toff, uint64_t R,
+                                                          long long* __restrict__ mm) {
+  if (blockIdx.y == B) {
+    offset_stats(toff, K, R, mm);
+    return;
+  }
   __shared__ uint32_t wsum[kBlock / 64][16];
   __shared__ uint64_t cnt[32];
   __shared__ uint32_t mx;
@@ -1233,42 +1277,6 @@ __global__ __launch_bounds__(kBlock) void k_encoder_stats(const uint32_t* __rest
     if (sb) atomicAdd((unsigned long long*)&shsum[(uint64_t)i * 33 + tid], (unsigned long long)sb);
   }
   if (tid == 0 && mx) atomicMax(&vmax[i], mx);
-}
-
-// Clears the statistics block of n words and sets the offset residue range at word mm_at to
-// (LLONG_MAX, LLONG_MIN), the identities of the minimum and maximum taken by k_offset_stats.
-__global__ void k_stats_init(uint64_t* __restrict__ st, uint64_t n, uint64_t mm_at) {
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n; i += (uint64_t)gridDim.x * blockDim.x)
-    st[i] = i == mm_at ? (uint64_t)LLONG_MAX : (i == mm_at + 1 ? (uint64_t)LLONG_MIN : 0);
-}
-
-// Offset residues delta_j = toff[j] - E_j: minimum and maximum over j in [0, K].
-__global__ __launch_bounds__(kBlock) void k_offset_stats(const uint64_t* __restrict__ toff, uint64_t K, uint64_t R,
-                                                         long long* __restrict__ mm) {
-  long long lmin = LLONG_MAX, lmax = LLONG_MIN;
-  for (uint64_t jj = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; jj <= K; jj += (uint64_t)gridDim.x * blockDim.x) {
-    long long d = (long long)(toff[jj] - expected_offset(jj, R));
-    lmin = min(lmin, d);
-    lmax = max(lmax, d);
-  }
-  __shared__ long long wmin[kBlock / 64], wmax[kBlock / 64];
-  for (int o = 32; o > 0; o >>= 1) {
-    lmin = min(lmin, (long long)__shfl_xor(lmin, o));
-    lmax = max(lmax, (long long)__shfl_xor(lmax, o));
-  }
-  if ((threadIdx.x & 63) == 0) {
-    wmin[threadIdx.x >> 6] = lmin;
-    wmax[threadIdx.x >> 6] = lmax;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {  // one pair of atomics per workgroup
-    for (int w = 1; w < kBlock / 64; w++) {
-      lmin = min(lmin, wmin[w]);
-      lmax = max(lmax, wmax[w]);
-    }
-    atomicMin(&mm[0], lmin);
-    atomicMax(&mm[1], lmax);
-  }
 }
 
 __global__ __launch_bounds__(kBlock) void k_pack_offsets(const uint64_t* __restrict__ toff, uint64_t K, uint64_t R,
@@ -1870,7 +1878,12 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
   PHOBIC_HIP(S.get(&sortedf, n));
   PHOBIC_HIP(S.get(&blist, K * B));
   PHOBIC_HIP(S.get(&nbk, K));
-  PHOBIC_HIP(S.get(&err, 4));
+  // the encoders' statistics (shifted sums B x 33, offset residue range 2, maxima B u32) and behind
+  // them the error words, so that one copy brings both back
+  const uint64_t nstat = (uint64_t)B * 33 + 2 + (B + 1) / 2;
+  uint64_t* stats;
+  PHOBIC_HIP(S.get(&stats, nstat + 2));
+  err = (uint32_t*)(stats + nstat);
   PHOBIC_HIP(S.get(&d64, 8));
   uint32_t* pilots_pm;  // partition-major rows from the search (every row written whole)
   if (keep) {
@@ -1918,6 +1931,9 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
     // second split takes slices of g rows' shares of a digit, about seven eighths of a tile, with
     // at most kMaxSliceBins (slice, bin) starts per digit.
     const bool two = dshift > 0;
+    // a single bin (up to G P keys: 10 000 at the defaults) is its own partition: the bucket sort reads
+    // the keys where they are, four launches less
+    const bool one = C == 1;
     const uint64_t T = str ? split_tile<ulonglong2>() : split_tile<uint64_t>();
     uint32_t g = (uint32_t)std::min<uint64_t>(R, std::max<uint64_t>(1, T * 7 * D / (8 * per)));
     g = std::max<uint32_t>(g, (uint32_t)(((uint64_t)R << dshift) + kMaxSliceBins - 1) / kMaxSliceBins);
@@ -1938,23 +1954,28 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
     }
     const size_t hist_lds = C * sizeof(uint32_t);
     tm.mark();  // 0
-    hipLaunchKernelGGL(k_build_clear, dim3(grid_for(std::max<uint64_t>(C, 8))), dim3(kBlock), 0, st, err, d64, ccnt, C);
+    hipLaunchKernelGGL(k_build_clear, dim3(grid_for(std::max<uint64_t>(C, 8))), dim3(kBlock), 0, st, err, d64, ccnt, C,
+                       one ? cbase : nullptr, n);
     if (str)
       hipLaunchKernelGGL(k_coarse_count<true>, dim3(R), dim3(kCoarseThreads), hist_lds, st, in.keys, in.bytes,
                          in.offs, stage, n, per, prm.hash_seed, K, (uint32_t)gshift, (uint32_t)C, dshift, D, ccnt,
                          hrow, drow);
-    else
+    else if (!one)
       hipLaunchKernelGGL(k_coarse_count<false>, dim3(R), dim3(kCoarseThreads), hist_lds, st, in.keys, in.bytes,
                          in.offs, stage, n, per, prm.hash_seed, K, (uint32_t)gshift, (uint32_t)C, dshift, D, ccnt,
                          hrow, drow);
     tm.mark();  // 1
-    hipLaunchKernelGGL(k_coarse_scan, dim3(1), dim3(1024), 0, st, ccnt, (uint32_t)C, cbase, cur);
-    hipLaunchKernelGGL(k_digit_offsets, dim3(D), dim3(1024), 0, st, drow, cbase, R, D, dshift, doff);
+    if (!one) {
+      hipLaunchKernelGGL(k_coarse_scan, dim3(1), dim3(1024), 0, st, ccnt, (uint32_t)C, cbase, cur);
+      hipLaunchKernelGGL(k_digit_offsets, dim3(D), dim3(1024), 0, st, drow, cbase, R, D, dshift, doff);
+    }
     if (two)
       hipLaunchKernelGGL(k_slice_offsets, dim3(D), dim3(1024), ((size_t)Q << dshift) * sizeof(uint32_t), st, hrow,
                          cbase, (uint32_t)C, R, g, Q, dshift, spos);
     tm.mark();  // 2
-    if (str) {
+    if (one) {
+      codes = stage;
+    } else if (str) {
       hipLaunchKernelGGL(k_split_digits<ulonglong2>, dim3(R), dim3(kSplitThreads), split_lds_bytes<ulonglong2>(),
                          st, (const ulonglong2*)stage, n, per, prm.hash_seed, K, (uint32_t)gshift, dshift, D, R,
                          doff, codes);
@@ -1982,7 +2003,7 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
                          (ulonglong2*)part_codes_out);
     else
       hipLaunchKernelGGL(k_segment_sort<kInKeys>, dim3((uint32_t)C), dim3(kSegThreads), kSegLdsBytes, st,
-                         (const void*)kcodes, prm.hash_seed, cbase, h->d_table, B, nbpad, (uint32_t)gshift, K,
+                         (const void*)(one ? in.keys : kcodes), prm.hash_seed, cbase, h->d_table, B, nbpad, (uint32_t)gshift, K,
                          (uint64_t)0, K, (uint64_t)0, seg_cap, sortedf, blist, nbk, off, err,
                          (ulonglong2*)part_codes_out);
     if (an != ad) {
@@ -2005,7 +2026,7 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
     if (str) PHOBIC_HIP(S.get(&stage, n));
     tm.mark();  // 0
     hipLaunchKernelGGL(k_build_clear, dim3(grid_for(std::max<uint64_t>(K + 1, 8))), dim3(kBlock), 0, st, err, d64,
-                       cnt, K + 1);
+                       cnt, K + 1, (uint64_t*)nullptr, n);
     hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, st, dinfo, (uint64_t)8, (uint64_t)0);
     const bool lds_parts = K <= kLdsParts;  // few partitions: LDS counts per chunk of keys
     const uint32_t chunks = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(2048, (n + 8191) / 8192));
@@ -2146,7 +2167,7 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
   unsigned long long* queue;
   PHOBIC_HIP(S.get(&queue, 1));
   tm.mark();  // 5
-  if (!wide && K > 1) {  // costly partitions first
+  if (!wide && K > 1 && !search_holds_all(sa, K)) {  // costly partitions first
     uint32_t *order, *oscr;
     PHOBIC_HIP(S.get(&order, K));
     PHOBIC_HIP(S.get(&oscr, order_scratch_words(K)));
@@ -2159,30 +2180,23 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
   {
     const uint64_t tiles = ((K + kTile - 1) / kTile) * ((B + kTile - 1) / kTile);
     hipLaunchKernelGGL(k_transpose_u32, dim3((uint32_t)std::min<uint64_t>(tiles, 65536)), dim3(kTile, kTile / 16),
-                       0, st, pilots_pm, K, (uint64_t)B, pilots);
+                       0, st, pilots_pm, K, (uint64_t)B, pilots, stats, nstat, (uint64_t)B * 33);
   }
-  // statistics -> host parameters, in one block so that one copy brings them back: the shifted sums
-  // (B x 33), the offset residue range (2), the maxima (B u32)
-  const uint64_t nstat = (uint64_t)B * 33 + 2 + (B + 1) / 2;
-  uint64_t* stats;
-  PHOBIC_HIP(S.get(&stats, nstat));
   uint64_t* shsum = stats;
   long long* dmm = (long long*)(stats + (uint64_t)B * 33);
   uint32_t* vmax = (uint32_t*)(stats + (uint64_t)B * 33 + 2);
   const uint64_t R = (uint64_t)(((unsigned __int128)total << 32) / K);
-  hipLaunchKernelGGL(k_stats_init, dim3(grid_for(nstat)), dim3(kBlock), 0, st, stats, nstat, (uint64_t)B * 33);
   // one workgroup per (chunk, encoder) in the statistics and the packing
   const uint64_t nch = (K + kPackChunk - 1) / kPackChunk;
   uint32_t* ccnt;
   PHOBIC_HIP(S.get(&ccnt, (uint64_t)B * nch * 32));
-  if (nch)
-    hipLaunchKernelGGL(k_encoder_stats, dim3((uint32_t)nch, B), dim3(kBlock), 0, st, pilots, K, shsum, vmax, ccnt);
-  hipLaunchKernelGGL(k_offset_stats, dim3(grid_for(K + 1, kBlock, 64)), dim3(kBlock), 0, st, toff, K, R, dmm);
+  hipLaunchKernelGGL(k_encoder_stats, dim3((uint32_t)nch, B + 1), dim3(kBlock), 0, st, pilots, K, shsum, vmax, ccnt, B,
+                     toff, R, dmm);
   PHOBIC_HIP(hipGetLastError());
   uint64_t* hstats;  // pinned
-  PHOBIC_HIP(S.host(&hstats, nstat));
-  PHOBIC_HIP(hipMemcpyAsync(hstats, stats, nstat * 8, hipMemcpyDeviceToHost, st));
-  PHOBIC_HIP(hipMemcpyAsync(hinfo, err, 4 * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+  PHOBIC_HIP(S.host(&hstats, nstat + 2));
+  PHOBIC_HIP(hipMemcpyAsync(hstats, stats, (nstat + 2) * 8, hipMemcpyDeviceToHost, st));
+  hinfo = (uint32_t*)(hstats + nstat);
   {  // while the device searches: take and give back a block of the likely image size (3 bits/key
      // and 40 per partition), so that the image allocation after the round trip finds mapped memory
      // in the pool instead of mapping pages on the critical path
@@ -2247,7 +2261,9 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
   hipLaunchKernelGGL(k_image_init, dim3(grid_for(nwords)), dim3(kBlock), 0, st, img, nwords, dhw,
                      (uint32_t)kHeaderWords, hdr[kHSecEnc], B);
   uint64_t* carries = nullptr;
-  if (rice && nch) {
+  if (rice && nch == 1) {
+    carries = dhw + kHeaderWords + B;  // one chunk (up to 4096 partitions): it starts where its encoder does
+  } else if (rice) {
     PHOBIC_HIP(S.get(&carries, (uint64_t)B * nch));
     if (B > nc)
       hipLaunchKernelGGL(k_chunk_carry, dim3(B - nc), dim3(kBlock), 0, st, ccnt, K, nch, dhw + kHeaderWords,
@@ -2256,8 +2272,7 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
   if (woff)
     hipLaunchKernelGGL(k_pack_offsets, dim3(grid_for(K + 1)), dim3(kBlock), 0, st, toff, K, R, dmin, woff,
                        img + hdr[kHSecOff]);
-  if (nch)
-    hipLaunchKernelGGL(k_pack_values, dim3((uint32_t)nch, B), dim3(kPackThreads), 0, st, pilots, K,
+  hipLaunchKernelGGL(k_pack_values, dim3((uint32_t)nch, B), dim3(kPackThreads), 0, st, pilots, K,
                        img + hdr[kHSecEnc], carries, (uint32_t)rice, nc, img + hdr[kHSecData],
                        img + hdr[kHSecUnary], img + hdr[kHSecSel]);
   const uint64_t nvals = K * (B - nc);  // ones of the unary stream: the values of the Rice encoders
@@ -2851,7 +2866,7 @@ phobic_status build_batch_impl(const uint64_t* const* keys, const uint64_t* coun
   sa.fail_part = (unsigned long long*)(err + 4);
   sa.order = nullptr;
   tm.mark();  // 2
-  if (Ktot > 1) {  // costly partitions of all MPHFs first
+  if (Ktot > 1 && !search_holds_all(sa, Ktot)) {  // costly partitions of all MPHFs first
     uint32_t *order, *oscr;
     PHOBIC_HIP(S.get(&order, Ktot));
     PHOBIC_HIP(S.get(&oscr, order_scratch_words(Ktot)));

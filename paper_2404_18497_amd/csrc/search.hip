@@ -1010,6 +1010,7 @@ hipError_t launch_team(SearchArgs& sa, uint64_t items, uint32_t W, size_t lds, h
 //   lambda 7, larger P: 10 000 (100 partitions) 1622/1025/781/764, (1000) 1855/1404/1632/2762;
 //              20 000 (500) 2579/2157/1744/2478; 50 000 (200) 6020/4475/3236/2888; 100 000 (100)
 //              11923/8660/6366/5641
+constexpr uint32_t kTeamWavesPerCu = 24;
 uint32_t team_waves(const SearchArgs& sa, uint64_t items) {
   const uint64_t c = sa.cus;
   const float l = sa.bucket_keys;
@@ -1022,10 +1023,23 @@ uint32_t team_waves(const SearchArgs& sa, uint64_t items) {
   return items <= 64 * c && l >= 11.8f ? 4 : 1;
 }
 
-hipError_t launch_search(SearchArgs& sa, uint64_t items, hipStream_t st, unsigned long long* queue) {
-  const phobic_search_config cfg = search_config();
+// The wavefronts per partition of the launch: teams under the default shape, as many as fit the LDS.
+uint32_t team_size(SearchArgs& sa, uint64_t items, const phobic_search_config& cfg) {
   uint32_t W = cfg.waves_per_group == 1 && cfg.groups_per_cu == 0 ? team_waves(sa, items) : 1;
   while (W > 1 && size_team_lds(sa, W) > sa.lds_limit) W /= 2;
+  return W;
+}
+
+bool search_holds_all(SearchArgs& sa, uint64_t items) {
+  const uint32_t W = team_size(sa, items, search_config());
+  if (W == 1) return false;
+  const uint64_t teams = std::min<uint64_t>(kTeamWavesPerCu / W, sa.lds_limit / size_team_lds(sa, W));  // per CU
+  return items <= teams * sa.cus;
+}
+
+hipError_t launch_search(SearchArgs& sa, uint64_t items, hipStream_t st, unsigned long long* queue) {
+  const phobic_search_config cfg = search_config();
+  const uint32_t W = team_size(sa, items, cfg);
   if (W > 1) {
     const size_t lds = size_team_lds(sa, W);
     if (sa.max_m <= kTeamScratchBits) return launch_team<true, true>(sa, items, W, lds, st);
