@@ -87,7 +87,7 @@ inline void size_search_lds(SearchArgs& sa, uint32_t mm, uint32_t mb, uint32_t B
 // words, the bitmaps, a claim table with an entry per slot up to kTeamClaims, and per wavefront a
 // repeat scratch of up to kTeamScratchBits and a position buffer.
 constexpr uint32_t kTeamMaxWaves = 16;
-constexpr uint32_t kTeamCtlWords = 144;
+constexpr uint32_t kTeamCtlWords = 156;
 constexpr uint32_t kTeamClaims = 4096;
 constexpr uint32_t kTeamScratchBits = 8192;
 constexpr uint32_t kTeamShiftSlots = 1u << 16;  // smaller tables keep a shifted copy of the bitmap

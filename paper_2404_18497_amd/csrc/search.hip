@@ -913,13 +913,13 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(8, 
 }
 
 // A team of blockDim.x / 64 wavefronts per partition.
-template <bool kShift, bool kFew>
+template <bool kShift, bool kFew, bool kMany>
 __global__ __launch_bounds__(64 * kTeamMaxWaves) void k_search_team(SearchArgs a) {
   extern __shared__ __align__(16) uint32_t lds32[];
   const uint64_t x = blockIdx.x;
   if (x >= a.K) return;
   const uint64_t j = a.order ? (uint64_t)uniform(a.order[x]) : x;
-  search_team<kShift, kFew>(a, j, lds32, uniform(threadIdx.x >> 6), threadIdx.x & 63, uniform(blockDim.x >> 6));
+  search_team<kShift, kFew, kMany>(a, j, lds32, uniform(threadIdx.x >> 6), threadIdx.x & 63, uniform(blockDim.x >> 6));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -986,41 +986,51 @@ hipError_t order_partitions(SearchArgs& sa, uint32_t* order, uint32_t* scratch, 
   return hipGetLastError();
 }
 
-template <bool kShift, bool kFew>
+template <bool kShift, bool kFew, bool kMany>
 hipError_t launch_team(SearchArgs& sa, uint64_t items, uint32_t W, size_t lds, hipStream_t st) {
   sa.queue = nullptr;
-  (void)allow_lds(k_search_team<kShift, kFew>, lds);
-  hipLaunchKernelGGL((k_search_team<kShift, kFew>), dim3((uint32_t)items), dim3(64 * W), lds, st, sa);
+  (void)allow_lds(k_search_team<kShift, kFew, kMany>, lds);
+  hipLaunchKernelGGL((k_search_team<kShift, kFew, kMany>), dim3((uint32_t)items), dim3(64 * W), lds, st, sa);
   return hipGetLastError();
 }
 
 // Wavefronts per partition under the default shape (1: the one-wavefront kernels).  A team pays while the
 // launch leaves wavefront slots empty, and longer the more pilots a bucket tries (keys per bucket,
 // lambda): it issues 1.5 to 3 times the instructions per partition.  A CU holds three teams of eight
-// or six of four (77 registers).  Search times in us, P = 2500, one wavefront / 4 / 8 / 16 per partition:
+// or six of four (77 registers), of the kMany variant two and four (104).  Search times in us, P = 2500,
+// one wavefront / 4 / 8 / 16 per partition (many: the kMany variant):
 //   lambda 5:  160 partitions 457/284/218/233, 520: 631/365/331/575, 1500: 491/497/613/1189, 3000: 533/908
-//   lambda 7:  1: 449/245/223/263, 160: 598/327/312/363, 520: 704/389/394/763, 1000: 829/459/616/1177,
-//              2000: 921/758/1018, 3000: 1291/1024/1455, 4000: 941/1646
-//   lambda 9:  160: 1937/836/697/769, 520: 2231/986/909/1712, 1000: 2466/1089/1329/2621,
-//              2000: 3458/1949/2322, 3000: 3461/2417/3335, 4000: 2680/2883/4018
+//   lambda 7:  1: 451/252/225/266, 160: 591/321/305/360 (many -/363/325/382), 520: 711/413/386/767,
+//              1000: 830/459/616/1177, 2000: 921/758/1018, 3000: 1291/1024/1455, 4000: 941/1646
+//   lambda 9:  160: 1934/829/692/769 (many -/827/642/659), 520: 2248/986/909/1721 (many -/1037/1008/1588),
+//              1000: 2432/1089/1329/2621, 2000: 3458/1949/2322, 3000: 3461/2417/3335, 4000: 2680/2883/4018
+//   lambda 10: 160: 5082/1770/1323/1332 (many -/1531/1085/1000), 520: 6500/2473/1865 (many -/2155/1624/2260)
+//   lambda 10.5: 160: 9039/2703/1919/1788 (many -/2448/1568/1329), 520: many 2172 against 2544 at eight
 //   lambda 11: 8000: 22738/20062/24754
-//   lambda 12: 160: 38796/9310/5955/4856, 520: 51465/13386/8625/8471, 1000: 53308/12325/9866/12746,
-//              2000: 50323/17567/16381/26222, 4000: 52056/27472/28338, 16000: 106844/86692/99983,
+//   lambda 12: 160: 38796/9310/5955/4856 (many -/9569/5640/4222), 520: 51465/13386/8484/8471 (many
+//              -/14696/9100/6499), 1000: 53308/12325/9443/12746 (many 10511 and 10374), 2000:
+//              50323/17567/16381/26222, 4000: 52056/27472/28338, 16000: 106844/86692/99983,
 //              40 000: 175300/205800/242200
 //   lambda 7, larger P: 10 000 (100 partitions) 1622/1025/781/764, (1000) 1855/1404/1632/2762;
-//              20 000 (500) 2579/2157/1744/2478; 50 000 (200) 6020/4475/3236/2888; 100 000 (100)
+//              20 000 (500) 2579/2157/1744/2478; 50 000 (200) 6008/4475/3236/2888; 100 000 (100)
 //              11923/8660/6366/5641
-constexpr uint32_t kTeamWavesPerCu = 24;
 uint32_t team_waves(const SearchArgs& sa, uint64_t items) {
   const uint64_t c = sa.cus;
   const float l = sa.bucket_keys;
-  if (items <= c) return l >= 10.8f || sa.max_m > kTeamScratchBits ? 16 : 8;
-  if (items <= 3 * c) return 8;
+  if (items <= c) return l >= 9.8f || sa.max_m > kTeamScratchBits ? 16 : 8;
+  if (items <= 3 * c) return l >= 11.5f && sa.max_m <= kTeamScratchBits ? 16 : 8;
   if (items <= 6 * c) return l >= 10.8f ? 8 : 4;
   if (items <= 12 * c) return l >= 6.0f ? 4 : 1;
   if (items <= 16 * c) return l >= 10.0f ? 4 : 1;
   if (items <= 32 * c) return l >= 10.8f ? 4 : 1;
   return items <= 64 * c && l >= 11.8f ? 4 : 1;
+}
+
+// Whether the team is the kMany variant: with few partitions its registers cost no team its place, and
+// from lambda 9 on (10 with up to three partitions per CU) the idle wavefronts' help is worth it.
+bool team_many(const SearchArgs& sa, uint64_t items) {
+  if (sa.max_m > kTeamScratchBits) return false;
+  return (items <= sa.cus && sa.bucket_keys >= 8.8f) || (items <= 3ull * sa.cus && sa.bucket_keys >= 9.8f);
 }
 
 // The wavefronts per partition of the launch: teams under the default shape, as many as fit the LDS.
@@ -1033,8 +1043,8 @@ uint32_t team_size(SearchArgs& sa, uint64_t items, const phobic_search_config& c
 bool search_holds_all(SearchArgs& sa, uint64_t items) {
   const uint32_t W = team_size(sa, items, search_config());
   if (W == 1) return false;
-  const uint64_t teams = std::min<uint64_t>(kTeamWavesPerCu / W, sa.lds_limit / size_team_lds(sa, W));  // per CU
-  return items <= teams * sa.cus;
+  const uint32_t waves = team_many(sa, items) ? 16 : 24;  // of the kernel, per CU
+  return items <= std::min<uint64_t>(waves / W, sa.lds_limit / size_team_lds(sa, W)) * sa.cus;
 }
 
 hipError_t launch_search(SearchArgs& sa, uint64_t items, hipStream_t st, unsigned long long* queue) {
@@ -1042,9 +1052,11 @@ hipError_t launch_search(SearchArgs& sa, uint64_t items, hipStream_t st, unsigne
   const uint32_t W = team_size(sa, items, cfg);
   if (W > 1) {
     const size_t lds = size_team_lds(sa, W);
-    if (sa.max_m <= kTeamScratchBits) return launch_team<true, true>(sa, items, W, lds, st);
-    return sa.max_m < kTeamShiftSlots ? launch_team<true, false>(sa, items, W, lds, st)
-                                      : launch_team<false, false>(sa, items, W, lds, st);
+    if (sa.max_m <= kTeamScratchBits)
+      return team_many(sa, items) ? launch_team<true, true, true>(sa, items, W, lds, st)
+                                  : launch_team<true, true, false>(sa, items, W, lds, st);
+    return sa.max_m < kTeamShiftSlots ? launch_team<true, false, false>(sa, items, W, lds, st)
+                                      : launch_team<false, false, false>(sa, items, W, lds, st);
   }
   if (sa.wide) {
     sa.queue = nullptr;

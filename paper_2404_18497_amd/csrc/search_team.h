@@ -10,8 +10,9 @@
 //   work      a wavefront whose candidate has lost a slot, or that has none, tests one unit of its
 //             bucket's pilots (in pilot order) and keeps the first that fits.  One that still holds a
 //             candidate, or has no bucket, takes a further unit of the first uncommitted bucket if
-//             that had none (units are handed out by a ticket; the lowest pilot found counts).  Every
-//             candidate claims its slots in `own` (the smallest claim wins: the later round, then
+//             that had none (units are handed out by a ticket; the lowest pilot found counts; kMany
+//             hands out single parts, also to those that found their candidate meanwhile).  Every
+//             candidate claims its slots in `claims` (the smallest claim wins: the later round, then
 //             the earlier bucket).
 //   check     in the run of buckets from the first uncommitted one on that hold a candidate, the
 //             first whose slots an earlier bucket claimed too ends the run.
@@ -27,9 +28,9 @@
 //
 // Bound: at lambda 7 the latency of a round (about 6500 cycles, 3.7 buckets committed, of which 4200
 // the longest unit of its eight wavefronts and 2300 claims, checks and marks); at lambda 12 the
-// instruction issue and LDS reads of 16 wavefronts' units on one CU.  One partition of 2500 keys:
-// 449 -> 223 us at lambda 7, 15.6 -> 2.5 ms at lambda 12; the times over partition counts stand at
-// team_waves.
+// parts' chains of LDS round trips (2100 cycles each, whatever the number of wavefronts) and the wait
+// for bucket r's.  One partition of 2500 keys: 449 -> 223 us at lambda 7, 15.6 -> 1.95 ms at lambda
+// 12; the times over partition counts stand at team_waves.
 
 constexpr uint32_t kTeamPacked = 32;  // buckets up to this size: several seeds per hash evaluation
 constexpr uint32_t kTeamPart = 128;   // displacement windows per part of such a bucket's pilots
@@ -64,27 +65,32 @@ __device__ __forceinline__ void team_failure(const SearchArgs& a, uint64_t j, ui
 // kShift: F2 has its shifted copy (position codes then hold slots below kTeamShiftSlots).
 // kFew: every table of the launch has at most kTeamScratchBits slots, so that a part of a packed bucket's
 // pilots is a number of whole seeds and the repeat scratch holds a bit per slot.
-template <bool kShift, bool kFew>
+// kMany: buckets try many pilots (lambda 9 and more): idle wavefronts help with bucket r, and a part's
+// two windows per lane go through the keys together, at 104 registers in place of 77.
+template <bool kShift, bool kFew, bool kMany>
 __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t j, uint32_t* const lds,
                                             const uint32_t wave, const uint32_t lane, const uint32_t W) {
   constexpr unsigned long long kNone = ~0ULL;
   typedef unsigned long long u64;
-  // control words: what every wavefront posted in this round and the last one (o, entry, next
-  // part, holds a candidate | failures), then per round modulo 3 (a round's set is cleared in the round before it)
-  // the helpers' best (pilot << 32 | unit), the helpers' tickets, the first bucket of the run that may
-  // not commit; then a flag for equal fingerprints and the counts
-  // of big buckets and of those with two keys or more
+  // control words: what every wavefront posted in this round and the last one (o, entry, next part,
+  // holds a candidate | failures); then per round modulo 3 (a round's set is cleared in the round before
+  // it) the helpers' best (pilot << 32 | part), the helpers' tickets, the first bucket of the run that may
+  // not commit and, for kMany, the state of bucket r and its place, entry and first part for helpers; then
+  // a flag for equal fingerprints and the counts of big buckets and of those with two keys or more
   uint32_t* const post = lds;
   u64* const best = (u64*)(lds + 8 * kTeamMaxWaves);
   uint32_t* const ticket = lds + 8 * kTeamMaxWaves + 6;
   uint32_t* const conflict = ticket + 3;
-  uint32_t* const dupflag = conflict + 3;
+  uint32_t* const state = conflict + 3;
+  uint32_t* const wanted = state + 3;
+  uint32_t* const dupflag = wanted + 9;
   uint32_t* const counts = dupflag + 1;
-  static_assert(8 * kTeamMaxWaves + 6 + 6 + 3 <= kTeamCtlWords, "control words");
+  static_assert(8 * kTeamMaxWaves + 6 + 9 + 9 + 3 <= kTeamCtlWords, "control words");
+  enum : uint32_t { kUndecided, kWanted, kDone };  // bucket r in a round: help wanted, or no new parts
   uint32_t* const F2 = lds + kTeamCtlWords;
   uint32_t* const F2s = F2 + a.f2_words;  // kShift: F2 shifted by one word
-  uint32_t* const own = F2 + (kShift ? 2 : 1) * a.f2_words;
-  uint32_t* const scr = own + a.own_words + (size_t)wave * (a.team_scr + a.rb_cap);
+  uint32_t* const claims = F2 + (kShift ? 2 : 1) * a.f2_words;
+  uint32_t* const scr = claims + a.own_words + (size_t)wave * (a.team_scr + a.rb_cap);
   uint32_t* const rbuf = scr + a.team_scr;
   const uint32_t omask = a.own_words - 1;
   const PosCode<kShift> pc{4 * a.f2_words};
@@ -117,12 +123,13 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
     F2[w] = f2_init(w);
     if (kShift) F2s[w] = f2_init(w + 1);
   }
-  for (uint32_t w = tid; w < a.own_words; w += nthreads) own[w] = ~0u;
+  for (uint32_t w = tid; w < a.own_words; w += nthreads) claims[w] = ~0u;
   for (uint32_t w = lane; w < a.team_scr; w += 64) scr[w] = 0;
   if (tid < 3) {
     best[tid] = kNone;
     ticket[tid] = 0;
     conflict[tid] = ~0u;
+    state[tid] = kUndecided;
   }
   if (tid == 0) {
     *dupflag = 0;
@@ -184,6 +191,30 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
     for (int t = 0; t < kN; t++) w[t] = window((ev[t] >> 16) + loff, ev[t]);
 #pragma unroll
     for (int t = 0; t < kN; t++) acc &= w[t];
+  };
+  // the same for two windows per lane, with a list of positions each
+  auto keys_and2 = [&](const uint32_t* const (&rb)[2], uint64_t (&acc)[2], const uint32_t (&loff)[2], auto n) {
+    constexpr int kN = decltype(n)::value;
+    uint32_t ev[2][kN];
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+      for (int t = 0; t < kN; t += 4) {
+        const uint4 e4 = *(const uint4*)(rb[h] + t);
+        ev[h][t] = e4.x;
+        ev[h][t + 1] = e4.y;
+        ev[h][t + 2] = e4.z;
+        ev[h][t + 3] = e4.w;
+      }
+    uint64_t w[2][kN];
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+      for (int t = 0; t < kN; t++) w[h][t] = window((ev[h][t] >> 16) + loff[h], ev[h][t]);
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+#pragma unroll
+      for (int t = 0; t < kN; t++) acc[h] &= w[h][t];
   };
   // ANDs the windows of the szp encoded positions at rb (szp is 4 or a multiple of 8) into acc; the
   // ballot of the lanes with a bit left
@@ -354,50 +385,115 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
     const uint32_t nwin = kFew ? nu * NW : min(kTeamPart, NW - w0);
     rbuf[lane] = pc.enc(pos_hash(f, (uint64_t)(s0 + (kFew ? lane >> lgS : 0u) + 1) * kPhi64, m));
     wave_sync();
-    uint32_t t0 = 0, r0 = 0;
-    for (uint32_t c = 0; c < nwin; c += 64) {
-      uint32_t dw, t;
-      bool act;
-      if (kFew) {  // lane x of chunk c takes window c + x of the seeds' windows in pilot order
-        dw = r0 + lane_r;
-        t = t0 + lane_q;
-        if (dw >= NW) {
-          dw -= NW;
-          t++;
+    if constexpr (kMany) {
+      // Lane x takes windows x and 64 + x of the part, in pilot order over its seeds.  Both go through the
+      // keys together, all reads of eight keys in flight: a part is a chain of LDS round trips.
+      uint32_t t[2], dw[2];
+      uint64_t acc[2], bal[2];
+      const uint32_t* rb[2];
+      uint32_t loff[2];
+#pragma unroll
+      for (int h = 0; h < 2; h++) {
+        bool act;
+        if (kFew) {
+          dw[h] = h ? r64 + lane_r : lane_r;
+          t[h] = h ? q64 + lane_q : lane_q;
+          if (h && dw[h] >= NW) {
+            dw[h] -= NW;
+            t[h]++;
+          }
+          act = t[h] < nu && t[h] <= smax - s0;
+        } else {
+          dw[h] = w0 + 64 * h + lane;
+          t[h] = 0;
+          act = 64 * h + lane < nwin;
         }
-        act = t < nu && t <= smax - s0;
+        acc[h] = act ? win_mask(dw[h] * 64) : 0ULL;
+        rb[h] = rbuf + (act ? t[h] * S : 0u);
+        loff[h] = act ? dw[h] * 8 : 0u;
+      }
+      if (S == 4) {
+        keys_and2(rb, acc, loff, std::integral_constant<int, 4>());
       } else {
-        dw = w0 + c + lane;
-        t = 0;
-        act = c + lane < nwin;
-      }
-      const uint32_t dlo = dw * 64;
-      uint64_t acc = act ? win_mask(dlo) : 0ULL;
-      uint64_t bal = keys_and(rbuf + (act ? t * S : 0u), acc, act ? dw * 8 : 0u, S > 8 ? (sz + 7) & ~7u : S);
-      while (bal) {
-        const uint32_t L = (uint32_t)__builtin_ctzll(bal);
-        const uint32_t tL = __builtin_amdgcn_readlane(t, L);
-        const uint32_t d = __builtin_amdgcn_readlane(dlo, L) + (uint32_t)__builtin_ctzll(lane_value64(acc, L));
-        const uint32_t sd = s0 + tL;
-        if (sd == smax && d > dlast) {
-          over = true;
-          return kNone;
+        for (uint32_t k = 0;;) {
+          keys_and2(rb, acc, loff, std::integral_constant<int, 8>());
+          k += 8;
+          if (k >= sz || uniform64(__ballot((acc[0] | acc[1]) != 0)) == 0) break;
+          rb[0] += 8;
+          rb[1] += 8;
         }
-        const uint32_t pos = pc.dec(rbuf[tL * S + (lane < sz ? lane : 0u)]);
-        if (!small_repeats(pos, sz)) {
-          fs = sd;
-          fd = d;
-          fslot = slot_of(pos, d);
-          return ((u64)(sd * m + d) << 32) | u;
-        }
-        bal &= ~uniform64(__ballot(t == tL));
       }
-      if (kFew) {
-        t0 += q64;
-        r0 += r64;
-        if (r0 >= NW) {
-          r0 -= NW;
-          t0++;
+#pragma unroll
+      for (int h = 0; h < 2; h++) bal[h] = uniform64(__ballot(acc[h] != 0));
+#pragma unroll
+      for (int h = 0; h < 2; h++) {
+        while (bal[h]) {
+          const uint32_t L = (uint32_t)__builtin_ctzll(bal[h]);
+          const uint32_t tL = __builtin_amdgcn_readlane(t[h], L);
+          const uint32_t d =
+              64 * __builtin_amdgcn_readlane(dw[h], L) + (uint32_t)__builtin_ctzll(lane_value64(acc[h], L));
+          const uint32_t sd = s0 + tL;
+          if (sd == smax && d > dlast) {
+            over = true;
+            return kNone;
+          }
+          const uint32_t pos = pc.dec(rbuf[tL * S + (lane < sz ? lane : 0u)]);
+          if (!small_repeats(pos, sz)) {
+            fs = sd;
+            fd = d;
+            fslot = slot_of(pos, d);
+            return ((u64)(sd * m + d) << 32) | u;
+          }
+          bal[0] &= ~uniform64(__ballot(t[0] == tL));
+          bal[1] &= ~uniform64(__ballot(t[1] == tL));
+        }
+      }
+    } else {
+      uint32_t t0 = 0, r0 = 0;
+      for (uint32_t c = 0; c < nwin; c += 64) {
+        uint32_t dw, t;
+        bool act;
+        if (kFew) {  // lane x of chunk c takes window c + x of the seeds' windows in pilot order
+          dw = r0 + lane_r;
+          t = t0 + lane_q;
+          if (dw >= NW) {
+            dw -= NW;
+            t++;
+          }
+          act = t < nu && t <= smax - s0;
+        } else {
+          dw = w0 + c + lane;
+          t = 0;
+          act = c + lane < nwin;
+        }
+        const uint32_t dlo = dw * 64;
+        uint64_t acc = act ? win_mask(dlo) : 0ULL;
+        uint64_t bal = keys_and(rbuf + (act ? t * S : 0u), acc, act ? dw * 8 : 0u, S > 8 ? (sz + 7) & ~7u : S);
+        while (bal) {
+          const uint32_t L = (uint32_t)__builtin_ctzll(bal);
+          const uint32_t tL = __builtin_amdgcn_readlane(t, L);
+          const uint32_t d = __builtin_amdgcn_readlane(dlo, L) + (uint32_t)__builtin_ctzll(lane_value64(acc, L));
+          const uint32_t sd = s0 + tL;
+          if (sd == smax && d > dlast) {
+            over = true;
+            return kNone;
+          }
+          const uint32_t pos = pc.dec(rbuf[tL * S + (lane < sz ? lane : 0u)]);
+          if (!small_repeats(pos, sz)) {
+            fs = sd;
+            fd = d;
+            fslot = slot_of(pos, d);
+            return ((u64)(sd * m + d) << 32) | u;
+          }
+          bal &= ~uniform64(__ballot(t == tL));
+        }
+        if (kFew) {
+          t0 += q64;
+          r0 += r64;
+          if (r0 >= NW) {
+            r0 -= NW;
+            t0++;
+          }
         }
       }
     }
@@ -432,7 +528,7 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
   };
 
   // The buckets of one key, in order (wavefront 0): key i takes the first free slot at or after its
-  // position.  The free slots are listed once (in `own`) and live on as a bitmap over their ranks, a
+  // position.  The free slots are listed once (in `claims`) and live on as a bitmap over their ranks, a
   // word per lane; a key's first rank comes from a search in the list, 64 keys at a time, and the
   // walk itself only reads lanes.  More free slots than that (non-minimal tables) are scanned.
   auto singles = [&]() {
@@ -446,7 +542,7 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
         uint64_t v = x * 64 < m ? (((uint64_t)F2[2 * x + 1] << 32) | F2[2 * x]) & win_mask(x * 64) : 0ULL;
         const uint32_t c = (uint32_t)__popcll(v);
         const uint32_t inc = wave_prefix(c, lane);
-        for (uint32_t at = base + inc - c; v; v &= v - 1) own[at++] = x * 64 + (uint32_t)__builtin_ctzll(v);
+        for (uint32_t at = base + inc - c; v; v &= v - 1) claims[at++] = x * 64 + (uint32_t)__builtin_ctzll(v);
         base += __builtin_amdgcn_readlane(inc, 63);
       }
       alive = lane * 64 < Q ? (Q - lane * 64 >= 64 ? ~0ULL : (1ULL << (Q - lane * 64)) - 1) : 0ULL;
@@ -461,7 +557,7 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
         uint32_t lo = 0, hi = Q;  // the first rank whose slot is at or after p
         while (uniform64(__ballot(lo < hi))) {
           const uint32_t mid = min((lo + hi) >> 1, Q - 1);
-          const bool below = own[mid] < p;
+          const bool below = claims[mid] < p;
           if (lo < hi) {
             if (below) lo = mid + 1; else hi = mid;
           }
@@ -482,7 +578,7 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
           if (lane == x) alive &= ~(1ULL << b);
           if (lane == k) mine = x * 64 + b;
         }
-        slot = own[mine];
+        slot = claims[mine];
       } else {
         for (uint32_t k = 0; k < cnt; k++) {
           const uint32_t pk = __builtin_amdgcn_readlane(p, k);
@@ -576,7 +672,7 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
       }
       return uniform64(__ballot(hit)) != 0;
     };
-    bool help = false;  // bucket r had no candidate after the last round: its next unit starts at part hu
+    bool help = false;  // !kMany: bucket r had no candidate after the last round: its next unit starts at hu
     uint32_t hu = 0;
     uint4 pv{0, 0, 0, 0};  // lane x: what wavefront x mod W posted last
     while (r < limit) {
@@ -585,63 +681,141 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
         best[n3] = kNone;
         ticket[n3] = 0;
         conflict[n3] = ~0u;
+        state[n3] = kUndecided;
       }
       // ---- work ----
-      const bool mine = idx < limit;
+      const bool mine = idx < limit, first = wave == w0;
       const uint32_t order = idx - r;
       const uint32_t claim = ~(round * kTeamMaxWaves + (kTeamMaxWaves - 1 - order));
       if (mine && has && any_slot([&](uint32_t t) { return is_taken(t); })) has = false;
-      const bool my_work = mine && !has;
-      uint32_t fmark = 0, hx = 0;
-      if (my_work || help) {
-        uint32_t we = e, wo = o, wu = u;
-        uint64_t wf = f;
-        if (!my_work) {
-          uint32_t tk = 0;
-          if (lane == 0) tk = atomicAdd(&ticket[b3], 1u);
-          wo = __builtin_amdgcn_readlane(pv.x, w0);
-          we = __builtin_amdgcn_readlane(pv.y, w0);
-          hx = unit_parts(kBig, hu);
-          wu = hu + hx * (1 + uniform(tk));
-          wf = load_f(we, wo);
+      uint32_t fmark = 0;
+      if constexpr (!kMany) {  // help in units, handed out to those that start the round idle
+        const bool my_work = mine && !has;
+        uint32_t hx = 0;
+        if (my_work || help) {
+          uint32_t we = e, wo = o, wu = u;
+          uint64_t wf = f;
+          if (!my_work) {
+            uint32_t tk = 0;
+            if (lane == 0) tk = atomicAdd(&ticket[b3], 1u);
+            wo = __builtin_amdgcn_readlane(pv.x, w0);
+            we = __builtin_amdgcn_readlane(pv.y, w0);
+            hx = unit_parts(kBig, hu);
+            wu = hu + hx * (1 + uniform(tk));
+            wf = load_f(we, wo);
+          }
+          const uint32_t parts = my_work ? unit_parts(kBig, wu) : hx;
+          bool over = false, dup = false;
+          u64 c = kNone;
+          for (uint32_t i = 0; i < parts && c == kNone && !over; i++)
+            c = kBig ? big_part(a.fp + kb + wo, wf, we >> 16, wo, wu + i, over, dup)
+                     : packed_part(wf, we >> 16, wu + i, over);
+          if (!my_work) {
+            if (c != kNone && lane == 0) atomicMin(&best[b3], c);
+          } else if (c != kNone) {
+            has = true;
+            u = (uint32_t)c;
+            cp = (uint32_t)(c >> 32);
+            cs = fs;
+            cd = fd;
+            ct = fslot;
+          } else {
+            if (!kBig && u == 0 && small_dup(f, e >> 16)) dup = true;
+            u += parts;
+            fmark = dup ? 2u : (over ? 4u : 0u);
+          }
         }
-        const uint32_t parts = my_work ? unit_parts(kBig, wu) : hx;
-        bool over = false, dup = false;
-        u64 c = kNone;
-        for (uint32_t i = 0; i < parts && c == kNone && !over; i++)
-          c = kBig ? big_part(a.fp + kb + wo, wf, we >> 16, wo, wu + i, over, dup)
-                   : packed_part(wf, we >> 16, wu + i, over);
-        if (!my_work) {
-          if (c != kNone && lane == 0) atomicMin(&best[b3], c);
-        } else if (c != kNone) {
-          has = true;
-          u = (uint32_t)c;
-          cp = (uint32_t)(c >> 32);
-          cs = fs;
-          cd = fd;
-          ct = fslot;
-        } else {
-          if (!kBig && u == 0 && small_dup(f, e >> 16)) dup = true;
-          u += parts;
-          fmark = dup ? 2u : (over ? 4u : 0u);
+      } else {  // help in single parts, as long as bucket r's own wavefront has more than one to go
+        bool own = mine && !has;
+        uint32_t parts = 0;
+        if (first) {
+          parts = unit_parts(kBig, u);
+          // help is wanted until the last part starts: nobody starts one that would end after it
+          const bool ask = own && parts > 1;
+          if (ask && lane == 0) {
+            wanted[3 * b3] = o;
+            wanted[3 * b3 + 1] = e;
+            wanted[3 * b3 + 2] = u + parts;
+          }
+          wave_sync();
+          if (lane == 0) state[b3] = ask ? kWanted : kDone;
         }
+        uint64_t hf = 0;  // the lane's fingerprint of the helped bucket, once loaded
+        uint32_t he = 0, ho = 0, hp = 0;
+        for (uint32_t left = parts;;) {
+          uint32_t we = e, wo = o, wu = u;
+          uint64_t wf = f;
+          if (!own) {
+            if (first) break;
+            const uint32_t st = uniform(state[b3]);
+            if (st == kDone) break;
+            if (st == kUndecided) continue;  // bucket r's wavefront decides after one look at its candidate
+            if (uniform64(best[b3]) != kNone) break;
+            if (he == 0) {
+              ho = uniform(wanted[3 * b3]);
+              he = uniform(wanted[3 * b3 + 1]);
+              hp = uniform(wanted[3 * b3 + 2]);
+              hf = load_f(he, ho);
+            }
+            uint32_t tk = 0;
+            if (lane == 0) tk = atomicAdd(&ticket[b3], 1u);
+            we = he;
+            wo = ho;
+            wu = hp + uniform(tk);
+            wf = hf;
+          }
+          bool over = false, dup = false;
+          const u64 c = kBig ? big_part(a.fp + kb + wo, wf, we >> 16, wo, wu, over, dup)
+                             : packed_part(wf, we >> 16, wu, over);
+          if (!own) {
+            if (c != kNone && lane == 0) atomicMin(&best[b3], c);
+            continue;
+          }
+          if (c != kNone) {
+            has = true;
+            cp = (uint32_t)(c >> 32);
+            cs = fs;
+            cd = fd;
+            ct = fslot;
+            own = false;
+          } else {
+            if (!kBig && u == 0 && small_dup(f, e >> 16)) dup = true;
+            u++;
+            fmark = dup ? 2u : (over ? 4u : 0u);
+            if (fmark) break;
+            if (first) {
+              if (--left == 0) break;
+              if (left == 1 && lane == 0) state[b3] = kDone;
+            } else if (uniform(state[b3]) == kDone) {
+              break;
+            }
+          }
+        }
+        if (first && lane == 0) state[b3] = kDone;
       }
       if (mine && has)
         any_slot([&](uint32_t t) {
-          atomicMin(&own[t & omask], claim);
+          atomicMin(&claims[t & omask], claim);
           return false;
         });
       if (lane == 0) {
         uint32_t* const p = post + (par * kTeamMaxWaves + wave) * 4;
-        p[0] = o;
-        p[1] = e;
-        p[2] = u;
+        if (!kMany) {
+          p[0] = o;
+          p[1] = e;
+          p[2] = u;
+        }
         p[3] = (mine && has ? 1u : 0u) | fmark;
       }
       __syncthreads();
       // ---- check ----
-      pv = *(const uint4*)(post + (par * kTeamMaxWaves + (lane & (W - 1))) * 4);
-      const uint32_t mine_wins = mine && order > 0 && has ? !any_slot([&](uint32_t t) { return own[t & omask] != claim; }) : 1u;
+      const uint32_t* const pp = post + (par * kTeamMaxWaves + (lane & (W - 1))) * 4;
+      if (kMany)
+        pv.w = pp[3];
+      else
+        pv = *(const uint4*)pp;
+      const bool wins =
+          mine && order > 0 && has ? !any_slot([&](uint32_t t) { return claims[t & omask] != claim; }) : true;
       if (__ballot(pv.w > 1)) {
         fl = __ballot((pv.w & 2) != 0) ? 1u : 2u;
         return;
@@ -649,11 +823,11 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
       const uint32_t wmask = (1u << W) - 1;
       const uint32_t flags = (uint32_t)uniform64(__ballot(pv.w != 0)) & wmask;
       uint32_t run = ((flags >> w0) | (flags << (W - w0))) & wmask;  // bit i: bucket r + i holds a candidate
-      if ((run & 1) == 0 && help) {
+      if ((kMany || help) && (run & 1) == 0) {
         const u64 bp = uniform64(best[b3]);
         if (bp != kNone) {  // a helper found bucket r's pilot: it commits alone, as it claimed nothing
           run = 1;
-          if (wave == w0) {
+          if (first) {
             has = true;
             cp = (uint32_t)(bp >> 32);
             cs = cp / m;
@@ -664,7 +838,7 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
       }
       uint32_t L = (uint32_t)__builtin_ctz(~run);
       if (L > 1) {
-        if (!mine_wins && order < L && lane == 0) atomicMin(&conflict[b3], order);
+        if (!wins && order < L && lane == 0) atomicMin(&conflict[b3], order);
         __syncthreads();
         L = min(L, uniform(conflict[b3]));
       }
@@ -680,23 +854,27 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
           advance();
         }
         r += L;
-        help = false;
-        if (L < W && r < limit) {  // the next first bucket, if no candidate was posted for it
-          help = __builtin_amdgcn_readlane(pv.w, r & (W - 1)) == 0;
-          hu = __builtin_amdgcn_readlane(pv.z, r & (W - 1));
+        if (!kMany) {
+          help = false;
+          if (L < W && r < limit) {  // the next first bucket, if no candidate was posted for it
+            help = __builtin_amdgcn_readlane(pv.w, r & (W - 1)) == 0;
+            hu = __builtin_amdgcn_readlane(pv.z, r & (W - 1));
+          }
         }
         __syncthreads();
-      } else {  // no pilot of bucket r in the parts up to here
+      } else if (kMany) {  // the helpers found none either
+        if (first) u += uniform(ticket[b3]);
+      } else {
         uint32_t next = __builtin_amdgcn_readlane(pv.z, w0);
         if (help) next += uniform(ticket[b3]) * unit_parts(kBig, hu);
         help = true;
         hu = next;
-        if (wave == w0) u = hu;
+        if (first) u = hu;
       }
       if (++round == 1u << 24) {  // claims hold 24 bits of the round
         round = 0;
         __syncthreads();
-        for (uint32_t w = tid; w < a.own_words; w += nthreads) own[w] = ~0u;
+        for (uint32_t w = tid; w < a.own_words; w += nthreads) claims[w] = ~0u;
         __syncthreads();
       }
       par ^= 1;

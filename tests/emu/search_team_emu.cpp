@@ -4,7 +4,7 @@
 // interleave; the workgroup barrier holds every lane until all have reached it.  Built with
 // AddressSanitizer over an LDS block of exactly the size the library gives the team.
 //
-// Usage: search_team_emu WAVES SEED IN OUT (IN and OUT as in search_emu.cpp)
+// Usage: search_team_emu WAVES SEED IN OUT; an odd SEED also picks the variant for many pilots per bucket (IN and OUT as in search_emu.cpp)
 #include <hip/hip_runtime.h>
 
 void emu_team_barrier();
@@ -29,17 +29,20 @@ using namespace phobic;
 namespace {
 SearchArgs g_sa;
 uint32_t *g_lds, g_W;
+bool g_many;  // odd SEED: the variant for many pilots per bucket
 bool g_done[1024];
 unsigned g_epoch[1024], g_released;
 
 void lane_main() {
   const unsigned me = threadIdx.x;
-  if (g_sa.max_m <= kTeamScratchBits)
-    search_team<true, true>(g_sa, 0, g_lds, me >> 6, me & 63, g_W);
+  if (g_sa.max_m <= kTeamScratchBits && g_many)
+    search_team<true, true, true>(g_sa, 0, g_lds, me >> 6, me & 63, g_W);
+  else if (g_sa.max_m <= kTeamScratchBits)
+    search_team<true, true, false>(g_sa, 0, g_lds, me >> 6, me & 63, g_W);
   else if (g_sa.max_m < kTeamShiftSlots)
-    search_team<true, false>(g_sa, 0, g_lds, me >> 6, me & 63, g_W);
+    search_team<true, false, false>(g_sa, 0, g_lds, me >> 6, me & 63, g_W);
   else
-    search_team<false, false>(g_sa, 0, g_lds, me >> 6, me & 63, g_W);
+    search_team<false, false, false>(g_sa, 0, g_lds, me >> 6, me & 63, g_W);
   g_done[me] = true;
 }
 }  // namespace
@@ -53,6 +56,7 @@ int main(int argc, char** argv) {
   if (argc != 5) return 2;
   g_W = (uint32_t)std::atoi(argv[1]);
   uint64_t rng = std::strtoull(argv[2], nullptr, 10) * 0x9E3779B97F4A7C15ULL + 1;
+  g_many = (std::atoi(argv[2]) & 1) != 0;
   FILE* f = std::fopen(argv[3], "rb");
   uint64_t h[5];
   if (!f || std::fread(h, 8, 5, f) != 5) return 3;

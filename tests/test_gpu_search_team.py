@@ -21,6 +21,7 @@ def _image(keys, prm):
     (100, 769, 7.0, (1, 1)), (100, 1536, 7.0, (1, 1)), (100, 1537, 7.0, (9, 10)), (100, 3072, 5.5, (1, 1)),
     (100, 3073, 7.0, (1, 1)),
     (2500, 2, 11.0, (1, 1)),  # sixteen wavefronts
+    (2500, 30, 9.0, (1, 1)), (500, 257, 10.0, (1, 1)),  # many pilots per bucket
     (8150, 1, 7.0, (1, 1)), (8200, 2, 7.0, (1, 1)),  # around 8192 slots: whole seeds or parts of one
     (10_000, 3, 6.0, (9, 10)), (70_000, 2, 7.0, (1, 1)),  # no shifted bitmap
 ])
