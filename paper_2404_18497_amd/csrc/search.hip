@@ -1014,13 +1014,25 @@ hipError_t launch_team(SearchArgs& sa, uint64_t items, uint32_t W, size_t lds, h
 //   lambda 7, larger P: 10 000 (100 partitions) 1622/1025/781/764, (1000) 1855/1404/1632/2762;
 //              20 000 (500) 2579/2157/1744/2478; 50 000 (200) 6008/4475/3236/2888; 100 000 (100)
 //              11923/8660/6366/5641
-uint32_t team_waves(const SearchArgs& sa, uint64_t items) {
+// Larger tables (more than 8192 slots) take the most wavefronts with which every partition has its team at
+// once: their bitmaps and position buffers leave few teams per CU, and with 2000 partitions of 50 000
+// teams of four took 20.1 ms where one wavefront each takes 12.7 (300 of them: 4.08 against 6.17 ms).
+// For the same reason more than six partitions per CU need, where the LDS and not the registers limits the
+// teams, room for most of them: 1750 partitions of 4000 keys (1280 teams at once) take 1084 us against
+// 1170 and 1285 of 7000 keys at lambda 9 (1024) 3451 against 4123, but 2400 of 5000 keys (1280) 1781
+// against 1141 and at lambda 9 4710 against 3983.
+uint32_t team_waves(SearchArgs& sa, uint64_t items) {
   const uint64_t c = sa.cus;
   const float l = sa.bucket_keys;
-  if (items <= c) return l >= 9.8f || sa.max_m > kTeamScratchBits ? 16 : 8;
-  if (items <= 3 * c) return l >= 11.5f && sa.max_m <= kTeamScratchBits ? 16 : 8;
+  auto teams = [&](uint32_t W) {  // that run at once
+    return std::min<uint64_t>(24 / W, sa.lds_limit / size_team_lds(sa, W)) * c;
+  };
+  if (sa.max_m > kTeamScratchBits) return items <= teams(16) ? 16 : (items <= teams(8) ? 8 : (items <= teams(4) ? 4 : 1));
+  if (items <= c) return l >= 9.8f ? 16 : 8;
+  if (items <= 3 * c) return l >= 11.5f ? 16 : 8;
   if (items <= 6 * c) return l >= 10.8f ? 8 : 4;
-  if (items <= 12 * c) return l >= 6.0f ? 4 : 1;
+  if (items <= 12 * c) return l >= 6.0f && (teams(4) == 6 * c || 5 * items <= 7 * teams(4)) ? 4 : 1;
+  if (sa.max_m > 4096) return 1;
   if (items <= 16 * c) return l >= 10.0f ? 4 : 1;
   if (items <= 32 * c) return l >= 10.8f ? 4 : 1;
   return items <= 64 * c && l >= 11.8f ? 4 : 1;
