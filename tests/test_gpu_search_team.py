@@ -47,6 +47,22 @@ def test_many_pilots_per_bucket(P, K, lam):
     assert np.array_equal(got, want)
 
 
+@pytest.mark.parametrize("P,K,lam", [(4000, 1792, 7.0), (4000, 1793, 7.0), (6500, 1400, 9.0), (20_000, 768, 7.0),
+                                     (20_000, 1025, 7.0), (50_000, 520, 7.0)])
+def test_teams_limited_by_lds(P, K, lam):
+    # around the counts from which the LDS no longer holds every partition's team; reference as above
+    keys = synth.u64_keys(P * K, K)
+    prm = binding.params(partition_size=P, lam=lam)
+    got = _image(keys, prm)
+    before = binding.get_search_config()
+    try:
+        binding.set_search_config(waves_per_group=2)
+        want = _image(keys, prm)
+    finally:
+        binding.set_search_config(**before)
+    assert np.array_equal(got, want)
+
+
 def test_batch_members_equal_the_oracle():
     # several MPHFs: pilots go to the members' encoder-major arrays
     sets = [synth.u64_keys(n, 50 + n) for n in (1, 700, 2500, 9001, 40_000)]
