@@ -218,6 +218,30 @@ __device__ __forceinline__ void query_codes(const QueryArgs& a, const TabT* __re
   }
 }
 
+// One lookup per thread, everything read through the caches: a launch of up to kQFew lookups has all of
+// them in flight at once, so it ends after one chain of dependent reads, and neither the workgroup's copy
+// to LDS nor four lookups in lockstep pay (k_query_u64, below).  A launch in a queue of them, us, before and
+// now, at lambda 7 (a call of the host costs 7.1 of them):
+//   10^6-key table:  1000 lookups 8.5 -> 7.1, 65 536 8.5 -> 7.1, 262 144 8.9 -> 7.0, 400 000 10.6 -> 8.1
+//   10^8-key table:  1000 8.7 -> 7.1, 65 536 10.0 -> 7.2, 262 144 16.4 -> 12.1, 400 000 21.2 -> 16.2, 600 000
+//                    27.4 -> 22.3, 10^6 35.2 -> 32.2, 10^7 273 -> 276, 10^8 2618 -> 2896
+// The line lies where the device's 2^19 threads are full: 10^6 lookups on each of two streams, which fill
+// it together, take 26.9 us a batch with k_query_u64 and 28.3 with this kernel.
+constexpr uint64_t kQFew = 1ull << 19;
+__global__ __launch_bounds__(kQBlock) void k_query_few(QueryArgs a, const uint64_t* __restrict__ keys, uint64_t n,
+                                                        uint64_t* __restrict__ out) {
+  const uint64_t x = blockIdx.x * (uint64_t)kQBlock + threadIdx.x;
+  if (x >= n) return;
+  if (a.n == 0) {
+    out[x] = 0;
+    return;
+  }
+  uint64_t hi[1], lo[1], res[1];
+  hash_key_u64(keys[x], a.seed, hi[0], lo[0]);
+  query_codes<1>(a, a.table, a.img + a.sec_enc, hi, lo, res);
+  out[x] = res[0];
+}
+
 constexpr int kQN = 4;
 constexpr uint32_t kQEncLds = 1024;  // encoders the LDS-staged query holds
 
@@ -371,7 +395,10 @@ extern "C" phobic_status phobic_query_u64(const phobic_mphf* h, const uint64_t* 
   if (!h) return fail(PHOBIC_E_INVALID, "null handle");
   if (n == 0) return PHOBIC_OK;
   if (!d_keys || !d_pos) return fail(PHOBIC_E_INVALID, "null key or output pointer");
-  if (h->qa.B <= kQEncLds)
+  if (n <= kQFew)
+    hipLaunchKernelGGL(k_query_few, dim3(query_grid(n)), dim3(kQBlock), 0, (hipStream_t)hip_stream, h->qa, d_keys, n,
+                       d_pos);
+  else if (h->qa.B <= kQEncLds)
     hipLaunchKernelGGL((k_query_u64<true>), dim3(query_grid(n, kQN)), dim3(kQBlock), 0, (hipStream_t)hip_stream,
                        h->qa, d_keys, n, d_pos);
   else

@@ -54,3 +54,20 @@ def test_positions_equal_the_oracle():
     binding.query_multi_u64(hs, ks, outs)
     for (name, _, _), o, want in zip(CASES, outs, wants):
         assert np.array_equal(o.cpu().numpy().view(np.uint64), want), name
+
+
+@pytest.mark.parametrize("kw,n", [(dict(lam=7.0), 100_000), (dict(lam=5.0, coding="compact"), 30_000),
+                                  (dict(lam=2.0, n_compact=16), 30_000), (dict(lam=7.0, alpha=(9, 10)), 30_000),
+                                  (dict(lam=6.0, partition_size=9000), 40_000), (dict(lam=7.0), 0)])
+def test_counts_around_the_kernels_line(kw, n):
+    # one lookup per thread up to 2^19 of them, four above; nothing is written past the last one
+    keys = synth.u64_keys(n, 11)
+    r = oracle.build_u64(keys, oracle.params(**kw), threads=8)
+    h = binding.build_u64(_dev(keys), binding.params(**kw))
+    q = np.resize(np.concatenate([keys, synth.u64_keys(1001, 98)]), (1 << 19) + 1)
+    want, dq = r.query_u64(q), _dev(q)
+    for count in (1, 63, 64, 255, 256, 257, 1025, (1 << 19) - 1, 1 << 19, (1 << 19) + 1):
+        out = torch.full((len(q) + 8,), -7, dtype=torch.int64, device="cuda")
+        h.query_u64(dq[:count], out=out[:count])
+        got = out.cpu().numpy()
+        assert np.array_equal(got[:count].view(np.uint64), want[:count]) and (got[count:] == -7).all(), count
