@@ -221,7 +221,7 @@ __device__ __forceinline__ void query_codes(const QueryArgs& a, const TabT* __re
 // One lookup per thread, everything read through the caches: a launch of up to kQFew lookups has all of
 // them in flight at once, so it ends after one chain of dependent reads, and neither the workgroup's copy
 // to LDS nor four lookups in lockstep pay (k_query_u64, below).  A launch in a queue of them, us, before and
-// now, at lambda 7 (a call of the host costs 7.1 of them):
+// now, at lambda 7, before k_query_mid (a call of the host costs 7.1 of them):
 //   10^6-key table:  1000 lookups 8.5 -> 7.1, 65 536 8.5 -> 7.1, 262 144 8.9 -> 7.0, 400 000 10.6 -> 8.1
 //   10^8-key table:  1000 8.7 -> 7.1, 65 536 10.0 -> 7.2, 262 144 16.4 -> 12.1, 400 000 21.2 -> 16.2, 600 000
 //                    27.4 -> 22.3, 10^6 35.2 -> 32.2, 10^7 273 -> 276, 10^8 2618 -> 2896
@@ -240,6 +240,40 @@ __global__ __launch_bounds__(kQBlock) void k_query_few(QueryArgs a, const uint64
   hash_key_u64(keys[x], a.seed, hi[0], lo[0]);
   query_codes<1>(a, a.table, a.img + a.sec_enc, hi, lo, res);
   out[x] = res[0];
+}
+
+// Two lookups per thread, the bucket table in LDS and the encoder words through the caches: calls that fill
+// the device a few times over.  The copy to LDS is 8 KB for 512 lookups instead of 11 for 1024, so less of a
+// call passes before its first image reads, and two lookups in lockstep leave room for more wavefronts.
+// us, k_query_u64 / this kernel, 10^8-key table at lambda 7, Rice: 10^6 lookups 36.4 / 34.1, 3*10^6 92.1 /
+// 87.9, 10^7 271.4 / 266.0, a batch of 10^6 on each of two streams 26.8 / 26.6; Compact: 21.8 / 20.9, 55.2 /
+// 52.7, 161.8 / 157.2, 21.8 / 21.1; 10^7-key table at lambda 5: 24.0 / 21.2, 57.1 / 52.2, 158.8 / 154.5, 15.2 /
+// 15.4.  10^8 lookups in one call take 2623 / 2665: the line is at kQMid.
+constexpr uint64_t kQMid = 1ull << 24;
+constexpr int kQMidN = 2;
+__global__ __launch_bounds__(kQBlock) void k_query_mid(QueryArgs a, const uint64_t* __restrict__ keys, uint64_t n,
+                                                        uint64_t* __restrict__ out) {
+  __shared__ uint32_t sT[kTableIntervals + 1];
+  const uint64_t x0 = blockIdx.x * (uint64_t)(kQBlock * kQMidN) + threadIdx.x;
+  if (a.n == 0) {
+    for (uint64_t x = x0; x < n && x < x0 + kQBlock * kQMidN; x += kQBlock) out[x] = 0;
+    return;
+  }
+  for (uint32_t x = threadIdx.x; x <= kTableIntervals; x += kQBlock) sT[x] = (uint32_t)a.table[x];
+  __syncthreads();
+  if (x0 >= n) return;
+  uint64_t hi[kQMidN], lo[kQMidN], res[kQMidN];
+#pragma unroll
+  for (int q = 0; q < kQMidN; q++) {
+    const uint64_t x = x0 + q * kQBlock;
+    hash_key_u64(keys[x < n ? x : x0], a.seed, hi[q], lo[q]);
+  }
+  query_codes<kQMidN>(a, (const uint32_t*)sT, a.img + a.sec_enc, hi, lo, res);
+#pragma unroll
+  for (int q = 0; q < kQMidN; q++) {
+    const uint64_t x = x0 + q * kQBlock;
+    if (x < n) out[x] = res[q];
+  }
 }
 
 constexpr int kQN = 4;
@@ -398,6 +432,9 @@ extern "C" phobic_status phobic_query_u64(const phobic_mphf* h, const uint64_t* 
   if (n <= kQFew)
     hipLaunchKernelGGL(k_query_few, dim3(query_grid(n)), dim3(kQBlock), 0, (hipStream_t)hip_stream, h->qa, d_keys, n,
                        d_pos);
+  else if (n <= kQMid)
+    hipLaunchKernelGGL(k_query_mid, dim3(query_grid(n, kQMidN)), dim3(kQBlock), 0, (hipStream_t)hip_stream, h->qa,
+                       d_keys, n, d_pos);
   else if (h->qa.B <= kQEncLds)
     hipLaunchKernelGGL((k_query_u64<true>), dim3(query_grid(n, kQN)), dim3(kQBlock), 0, (hipStream_t)hip_stream,
                        h->qa, d_keys, n, d_pos);

@@ -60,7 +60,7 @@ def test_positions_equal_the_oracle():
                                   (dict(lam=2.0, n_compact=16), 30_000), (dict(lam=7.0, alpha=(9, 10)), 30_000),
                                   (dict(lam=6.0, partition_size=9000), 40_000), (dict(lam=7.0), 0)])
 def test_counts_around_the_kernels_line(kw, n):
-    # one lookup per thread up to 2^19 of them, four above; nothing is written past the last one
+    # one lookup per thread up to 2^19 of them, two above; nothing is written past the last one
     keys = synth.u64_keys(n, 11)
     r = oracle.build_u64(keys, oracle.params(**kw), threads=8)
     h = binding.build_u64(_dev(keys), binding.params(**kw))
@@ -71,3 +71,16 @@ def test_counts_around_the_kernels_line(kw, n):
         h.query_u64(dq[:count], out=out[:count])
         got = out.cpu().numpy()
         assert np.array_equal(got[:count].view(np.uint64), want[:count]) and (got[count:] == -7).all(), count
+
+
+def test_counts_around_the_staged_kernels_line():
+    # two lookups per thread up to 2^24 of them, four above
+    keys = synth.u64_keys(30_000, 12)
+    for kw in (dict(lam=7.0), dict(lam=6.0, partition_size=9000)):
+        h = binding.build_u64(_dev(keys), binding.params(**kw))
+        want = oracle.build_u64(keys, oracle.params(**kw)).query_u64(keys)
+        dq, dw = _dev(keys).repeat(560)[:(1 << 24) + 1], _dev(want).repeat(560)[:(1 << 24) + 1]
+        for count in ((1 << 19) + 511, (1 << 19) + 257, 1 << 24, (1 << 24) + 1):
+            out = torch.full((len(dq) + 8,), -7, dtype=torch.int64, device="cuda")
+            h.query_u64(dq[:count], out=out[:count])
+            assert torch.equal(out[:count], dw[:count]) and bool((out[count:] == -7).all()), count
