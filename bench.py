@@ -258,7 +258,7 @@ def headline(args):
     else:
         per = query_ms / nlaunch
         achieved = 16.0 * min(batch, n) / (per * 1e-3) / 1e9
-        # the query instance that stages the bucket table and encoder words in LDS (B <= 1024)
+        # the query instance of calls of 2^19 to 2^24 lookups
         qkernel = "k_query_mid"
         roofline = {"kernel": qkernel, "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),

@@ -248,7 +248,8 @@ __global__ __launch_bounds__(kQBlock) void k_query_few(QueryArgs a, const uint64
 // us, k_query_u64 / this kernel, 10^8-key table at lambda 7, Rice: 10^6 lookups 36.4 / 34.1, 3*10^6 92.1 /
 // 87.9, 10^7 271.4 / 266.0, a batch of 10^6 on each of two streams 26.8 / 26.6; Compact: 21.8 / 20.9, 55.2 /
 // 52.7, 161.8 / 157.2, 21.8 / 21.1; 10^7-key table at lambda 5: 24.0 / 21.2, 57.1 / 52.2, 158.8 / 154.5, 15.2 /
-// 15.4.  10^8 lookups in one call take 2623 / 2665: the line is at kQMid.
+// 15.4.  10^8 lookups in one call take 2623 / 2665, hence the line at kQMid; as 100 calls that alternate between
+// two streams, each reading new keys, 2711 / 2759, the one loss for what single calls gain.
 constexpr uint64_t kQMid = 1ull << 24;
 constexpr int kQMidN = 2;
 __global__ __launch_bounds__(kQBlock) void k_query_mid(QueryArgs a, const uint64_t* __restrict__ keys, uint64_t n,
