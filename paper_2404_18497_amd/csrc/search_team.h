@@ -61,6 +61,32 @@ __device__ __forceinline__ void team_failure(const SearchArgs& a, uint64_t j, ui
   if (a.fail_part) atomicMin(a.fail_part, (unsigned long long)j);
 }
 
+// Words that one wavefront writes and others read between two barriers (the help protocol of kMany).  The
+// waiting loop reads nothing else, so only an atomic read obliges the compiler to read again; release and
+// acquire order the words that `state` publishes.  (The host emulation has one thread, whose wavefronts
+// change at collectives.)
+__device__ __forceinline__ uint32_t shared_acquire(const uint32_t* p) {
+#ifdef __HIP__
+  return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+#else
+  return *p;
+#endif
+}
+__device__ __forceinline__ unsigned long long shared_read(const unsigned long long* p) {
+#ifdef __HIP__
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+#else
+  return *p;
+#endif
+}
+__device__ __forceinline__ void shared_release(uint32_t* p, uint32_t v) {
+#ifdef __HIP__
+  __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+#else
+  *p = v;
+#endif
+}
+
 // Places every bucket of partition j; all W wavefronts (a power of two, at most kTeamMaxWaves) call it.
 // kShift: F2 has its shifted copy (position codes then hold slots below kTeamShiftSlots).
 // kFew: every table of the launch has at most kTeamScratchBits slots, so that a part of a packed bucket's
@@ -737,8 +763,7 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
             wanted[3 * b3 + 1] = e;
             wanted[3 * b3 + 2] = u + parts;
           }
-          wave_sync();
-          if (lane == 0) state[b3] = ask ? kWanted : kDone;
+          if (lane == 0) shared_release(&state[b3], ask ? kWanted : kDone);
         }
         uint64_t hf = 0;  // the lane's fingerprint of the helped bucket, once loaded
         uint32_t he = 0, ho = 0, hp = 0;
@@ -747,10 +772,10 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
           uint64_t wf = f;
           if (!own) {
             if (first) break;
-            const uint32_t st = uniform(state[b3]);
+            const uint32_t st = uniform(shared_acquire(&state[b3]));
             if (st == kDone) break;
             if (st == kUndecided) continue;  // bucket r's wavefront decides after one look at its candidate
-            if (uniform64(best[b3]) != kNone) break;
+            if (uniform64(shared_read(&best[b3])) != kNone) break;
             if (he == 0) {
               ho = uniform(wanted[3 * b3]);
               he = uniform(wanted[3 * b3 + 1]);
@@ -785,13 +810,13 @@ __device__ __forceinline__ void search_team(const SearchArgs& a, const uint64_t 
             if (fmark) break;
             if (first) {
               if (--left == 0) break;
-              if (left == 1 && lane == 0) state[b3] = kDone;
-            } else if (uniform(state[b3]) == kDone) {
+              if (left == 1 && lane == 0) shared_release(&state[b3], kDone);
+            } else if (uniform(shared_acquire(&state[b3])) == kDone) {
               break;
             }
           }
         }
-        if (first && lane == 0) state[b3] = kDone;
+        if (first && lane == 0) shared_release(&state[b3], kDone);
       }
       if (mine && has)
         any_slot([&](uint32_t t) {
