@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <vector>
 
+#include "image_check.h"
 #include "phobic_internal.h"
 
 namespace phobic {
@@ -242,215 +243,23 @@ void fill_query_args(phobic_mphf* h) {
   a.ncompact = (uint32_t)H[kHNcompact];
 }
 
-static uint64_t host_bits(const uint64_t* w, uint64_t pos, uint32_t width) {
-  if (width == 0) return 0;
-  uint64_t idx = pos >> 6;
-  uint32_t sh = (uint32_t)(pos & 63);
-  uint64_t v = w[idx] >> sh;
-  if (sh + width > 64) v |= w[idx + 1] << (64 - sh);
-  return width == 64 ? v : (v & ((1ULL << width) - 1));
-}
-
-static uint32_t host_bit_length(uint64_t v) { return v ? 64 - __builtin_clzll(v) : 0; }
-
-// Checks that an image is internally consistent, so the query kernel never reads outside it: its header
-// and section extents (check_header), then everything in the sections, on the host (check_sections) or,
-// for the uploaded image, on the device (k_check_sections).
-static phobic_status bad_image(const char* what) {
-  return fail(PHOBIC_E_FORMAT, std::string("malformed image: ") + what);
-}
-
-static phobic_status check_header(const uint64_t* w, uint64_t nwords) {
-  auto bad = bad_image;
-  if (nwords < kHeaderWords || w[kHMagic] != kMagic) return bad("magic");
-  if (w[kHWords] != nwords) return bad("length");
-  const uint64_t n = w[kHN], K = w[kHK], B = w[kHB], total = w[kHTotal];
-  const uint64_t coding = w[kHCoding] & 0xFF, bfn = w[kHCoding] >> 8;
-  if (K == 0 || B == 0 || B > 65535 || coding > 1 || bfn > PHOBIC_BF_UNIFORM || total < n) return bad("sizes");
-  const uint64_t c = w[kHNcompact];  // Compact encoders before the Rice ones (Rice images only)
-  if (c > B || (coding != PHOBIC_IC_RICE && c != 0)) return bad("mixed coding");
-  const uint32_t an = (uint32_t)w[kHAlpha], ad = (uint32_t)(w[kHAlpha] >> 32);
-  if (an == 0 || ad == 0 || an > ad || w[kHP] == 0 || w[kHP] > 0xFFFFFFFFULL) return bad("parameters");
-  double lambda;
-  std::memcpy(&lambda, &w[kHLambda], 8);
-  if (!(lambda > 0.0) || !std::isfinite(lambda) || (uint64_t)std::ceil((double)w[kHP] / lambda) != B)
-    return bad("lambda");
-  if (K != num_partitions(n, (uint32_t)w[kHP])) return bad("partition count");
-  if (w[kHWoff] > 64 || w[kHWremap] > 64) return bad("widths");
-  const uint64_t so = w[kHSecOff], se = w[kHSecEnc], sd = w[kHSecData], su = w[kHSecUnary], ss = w[kHSecSel],
-                 sr = w[kHSecRemap];
-  if (so != kHeaderWords) return bad("section order");
-  if (se != so + ((K + 1) * w[kHWoff] + 63) / 64 + 1 || sd != se + B + 1 || su < sd || ss < su || sr < ss ||
-      sr > nwords)
-    return bad("section layout");
-  return PHOBIC_OK;
-}
-
-static phobic_status check_sections(const uint64_t* w, uint64_t nwords) {
-  auto bad = bad_image;
-  const uint64_t n = w[kHN], K = w[kHK], B = w[kHB], total = w[kHTotal], c = w[kHNcompact];
-  const uint64_t coding = w[kHCoding] & 0xFF;
-  const uint64_t so = w[kHSecOff], se = w[kHSecEnc], sd = w[kHSecData], su = w[kHSecUnary], ss = w[kHSecSel],
-                 sr = w[kHSecRemap];
-  // offsets: 0 first, total last, non-decreasing
-  uint64_t prev = 0;
-  for (uint64_t j = 0; j <= K; j++) {
-    uint64_t o = phobic::expected_offset_host(j, w[kHR]) + w[kHDmin] + host_bits(w + so, j * w[kHWoff], (uint32_t)w[kHWoff]);
-    if ((j == 0 && o != 0) || o < prev || (j == K && o != total)) return bad("offsets");
-    prev = o;
-  }
-  // encoders: payload inside the data section
-  const uint64_t data_bits = (su - sd - 1) * 64;
-  for (uint64_t i = 0; i < B; i++) {
-    const uint64_t e = w[se + i];
-    const uint32_t wd = (uint32_t)(e & 0xFF);
-    if (wd > 32 || (e >> 8) + (uint64_t)wd * K > data_bits) return bad("encoder table");
-  }
-  const uint64_t nvals = K * (B - c);  // values of the Rice encoders: one one each in the unary stream
-  if (coding == PHOBIC_IC_RICE) {
-    const uint64_t ubits = w[kHUbits];
-    if (su + (ubits + 63) / 64 + 1 != ss) return bad("unary length");
-    uint64_t ones = 0;
-    for (uint64_t i = 0; i < (ubits + 63) / 64; i++) ones += __builtin_popcountll(w[su + i]);
-    if (ones != nvals || w[ss - 1] != 0) return bad("unary stream");
-    const uint64_t nsel = (nvals + kSelBlock - 1) / kSelBlock;
-    if (ss + nsel + 1 != sr) return bad("select length");
-    // every entry must hold exactly the position of one number kSelBlock s and the distances to ones
-    // kSelBlock s + kSelSub k: positions of every kSelSub-th one first
-    std::vector<uint64_t> p64((nvals + kSelSub - 1) / kSelSub);
-    uint64_t seen = 0, s_next = 0;
-    for (uint64_t i = 0; i < (ubits + 63) / 64 && s_next < p64.size(); i++) {
-      uint64_t x = w[su + i];
-      while (x && s_next < p64.size()) {
-        const uint64_t c = (uint64_t)__builtin_popcountll(x);
-        const uint64_t want = s_next * kSelSub;
-        if (seen + c <= want) {
-          seen += c;
-          break;
-        }
-        for (uint64_t skip = want - seen; skip; skip--) x &= x - 1;  // drop ones before the target
-        p64[s_next++] = i * 64 + (uint64_t)__builtin_ctzll(x);
-        seen = want + 1;
-        x &= x - 1;
-      }
-    }
-    if (s_next != p64.size()) return bad("select samples");
-    constexpr uint32_t per = kSelBlock / kSelSub;
-    for (uint64_t sb = 0; sb < nsel; sb++) {
-      const uint64_t a0 = p64[sb * per];
-      if (a0 >> 32) return bad("select range");
-      uint64_t want = a0;
-      for (uint32_t k = 1; k < per; k++) {
-        const uint64_t idx = sb * per + k;
-        const uint64_t rel = idx < p64.size() ? std::min<uint64_t>(p64[idx] - a0, kSelRelNone) : 0;
-        want |= rel << (32 + 10 * (k - 1));
-      }
-      if (w[ss + sb] != want) return bad("select samples");
-    }
-  } else if (su != ss || ss != sr) {
-    return bad("compact layout");
-  }
-  const uint64_t nremap = total - n;
-  if (w[kHNremap] != nremap || (nremap && w[kHWremap] != (n > 1 ? host_bit_length(n - 1) : 0)))
-    return bad("remap");
-  const uint64_t want_end = sr + (nremap ? (nremap * w[kHWremap] + 63) / 64 + 1 : 0);
-  if (want_end != nwords) return bad("remap length");
-  for (uint64_t g = 0; g < nremap; g++)
-    if (host_bits(w + sr, g * w[kHWremap], (uint32_t)w[kHWremap]) >= n) return bad("remap entries");
-  return PHOBIC_OK;
-}
-
-// The same checks on the device.  The select entries are checked segment by segment: entry s names a set
-// bit with exactly kSelBlock ones from there to the next entry's (the last one: the remaining ones to the
-// end), and none precede entry 0's, so by induction every entry names the one it should; the three
-// distances follow from the ones after it.  Bound: one pass over the image (0.25 B per key).
-enum : uint32_t { kBadOffsets, kBadEncoders, kBadUnary, kBadSelect, kBadRemap };
-
-__global__ __launch_bounds__(256) void k_check_clear(uint32_t* flag) {
+// The uploaded image's header becomes the checked one.
+__global__ __launch_bounds__(64) void k_check_start(uint64_t* __restrict__ img, ImageHeader h,
+                                                    uint32_t* __restrict__ flag) {
+  if (threadIdx.x < kHeaderWords) img[threadIdx.x] = h.w[threadIdx.x];
   if (threadIdx.x == 0) *flag = 0;
 }
 
-__global__ __launch_bounds__(256) void k_check_sections(const uint64_t* __restrict__ w, uint32_t* __restrict__ flag) {
-  const uint64_t tid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x, nt = (uint64_t)gridDim.x * blockDim.x;
-  const uint64_t n = w[kHN], K = w[kHK], B = w[kHB], total = w[kHTotal], R = w[kHR], dmin = w[kHDmin];
-  const uint64_t sd = w[kHSecData], su = w[kHSecUnary];
-  const uint32_t woff = (uint32_t)w[kHWoff];
-  uint32_t bad = 0;
-  for (uint64_t j = tid; j <= K; j += nt) {
-    const uint64_t* off = w + w[kHSecOff];
-    const uint64_t o = expected_offset(j, R) + dmin + get_bits(off, j * woff, woff);
-    if (j == 0 ? o != 0 : o < expected_offset(j - 1, R) + dmin + get_bits(off, (j - 1) * woff, woff)) bad |= 1u << kBadOffsets;
-    if (j == K && o != total) bad |= 1u << kBadOffsets;
-  }
-  const uint64_t data_bits = (su - sd - 1) * 64;
-  for (uint64_t i = tid; i < B; i += nt) {
-    const uint64_t e = w[w[kHSecEnc] + i];
-    const uint32_t wd = (uint32_t)(e & 0xFF);
-    if (wd > 32 || (e >> 8) + (uint64_t)wd * K > data_bits) bad |= 1u << kBadEncoders;
-  }
-  if ((w[kHCoding] & 0xFF) == PHOBIC_IC_RICE) {
-    const uint64_t nvals = K * (B - w[kHNcompact]), nsel = (nvals + kSelBlock - 1) / kSelBlock;
-    const uint64_t* un = w + su;
-    const uint64_t* sel = w + w[kHSecSel];
-    const uint64_t U = (w[kHUbits] + 63) / 64, ubits = U * 64;
-    if (tid == 0 && un[U] != 0) bad |= 1u << kBadUnary;
-    if (nsel == 0)
-      for (uint64_t x = tid; x < U; x += nt)
-        if (un[x]) bad |= 1u << kBadUnary;
-    for (uint64_t s = tid; s < nsel; s += nt) {
-      const uint64_t entry = sel[s], a = entry & 0xFFFFFFFFULL;
-      const uint64_t end = s + 1 < nsel ? sel[s + 1] & 0xFFFFFFFFULL : ubits;
-      const uint64_t want = s + 1 < nsel ? kSelBlock : nvals - s * kSelBlock;
-      if (a >= ubits || end <= a || end > ubits || !((un[a >> 6] >> (a & 63)) & 1)) {
-        bad |= 1u << kBadSelect;
-        continue;
-      }
-      if (s == 0) {
-        uint64_t before = un[a >> 6] & ((1ULL << (a & 63)) - 1);
-        for (uint64_t x = 0; x < a >> 6; x++) before |= un[x];
-        if (before) bad |= 1u << kBadSelect;
-      }
-      uint64_t word = a >> 6, x = un[word] & (~0ULL << (a & 63)), seen = 0, out = a;
-      uint32_t k = 1;  // the next distance: one number kSelSub k from the entry's on
-      for (;; x = un[++word]) {
-        const bool last = word == (end - 1) >> 6;
-        if (last && (end & 63)) x &= (1ULL << (end & 63)) - 1;
-        const uint32_t c = __popcll(x);
-        for (; k < kSelBlock / kSelSub && k * kSelSub < want && seen + c > k * kSelSub; k++) {
-          const uint64_t rel = word * 64 + select_in_word(x, (uint32_t)(k * kSelSub - seen)) - a;
-          out |= (rel < kSelRelNone ? rel : kSelRelNone) << (32 + 10 * (k - 1));
-        }
-        seen += c;
-        if (last) break;
-      }
-      if (seen != want) bad |= 1u << kBadUnary;
-      if (out != entry) bad |= 1u << kBadSelect;
-    }
-  }
-  const uint64_t nremap = total - n;
-  const uint32_t wr = (uint32_t)w[kHWremap];
-  for (uint64_t g = tid; g < nremap; g += nt)
-    if (get_bits(w + w[kHSecRemap], g * wr, wr) >= n) bad |= 1u << kBadRemap;
+__global__ __launch_bounds__(256) void k_check_sections(const uint64_t* __restrict__ w, ImageHeader h,
+                                                        uint32_t* __restrict__ flag) {
+  const uint32_t bad = check_part(w, h, blockIdx.x * (uint64_t)blockDim.x + threadIdx.x,
+                                  (uint64_t)gridDim.x * blockDim.x);
   if (bad) atomicOr(flag, bad);
 }
 
 // Images of fewer words are checked on the host, at about 4.5 ns a word (8900 words: 55 us a load); the
 // device's check and the round trip for its answer take 47 us at 16 500 words and 58 us at 57 000.
 constexpr uint64_t kDeviceCheckWords = 1 << 13;
-
-// Whether the sections of a checked header lie inside the image, each with its pad word, in arithmetic
-// that cannot wrap: what the device check reads.  (The host check refuses what does not fit.)
-static bool sections_fit(const uint64_t* w, uint64_t nwords) {
-  const uint64_t K = w[kHK], B = w[kHB], nremap = w[kHTotal] - w[kHN];
-  const uint64_t su = w[kHSecUnary], ss = w[kHSecSel], sr = w[kHSecRemap], bits = nwords * 64;
-  if (K >> 31 || w[kHUbits] > bits || (K + 1) * w[kHWoff] > bits || su <= w[kHSecData]) return false;
-  if (w[kHNremap] != nremap || (nremap && w[kHWremap] != host_bit_length(w[kHN] ? w[kHN] - 1 : 0))) return false;
-  if (nremap && (w[kHWremap] == 0 || nremap > bits / w[kHWremap])) return false;
-  if (sr + (nremap ? (nremap * w[kHWremap] + 63) / 64 + 1 : 0) != nwords) return false;
-  if ((w[kHCoding] & 0xFF) != PHOBIC_IC_RICE) return su == ss && ss == sr;
-  return su + (w[kHUbits] + 63) / 64 + 1 == ss &&
-         ss + (K * (B - w[kHNcompact]) + kSelBlock - 1) / kSelBlock + 1 == sr;
-}
 
 }  // namespace phobic
 
@@ -510,8 +319,9 @@ extern "C" phobic_status phobic_deserialize(const void* h_buf, uint64_t bytes, v
   if (!h_buf || bytes % 8 != 0) return fail(PHOBIC_E_FORMAT, "image size is not a whole number of words");
   const uint64_t nwords = bytes / 8;
   if (nwords < kHeaderWords) return bad_image("length");
-  uint64_t w[kHeaderWords];  // the header; the sections stay in h_buf
-  std::memcpy(w, h_buf, sizeof(w));
+  ImageHeader hdr;  // read once; the sections stay in h_buf
+  std::memcpy(hdr.w, h_buf, sizeof(hdr.w));
+  const uint64_t* const w = hdr.w;
   phobic_status s = check_header(w, nwords);
   if (s != PHOBIC_OK) return s;
   const bool on_device = nwords >= kDeviceCheckWords && sections_fit(w, nwords);
@@ -519,6 +329,7 @@ extern "C" phobic_status phobic_deserialize(const void* h_buf, uint64_t bytes, v
   if (!on_device) {
     copy.resize(nwords);
     std::memcpy(copy.data(), h_buf, bytes);
+    std::memcpy(copy.data(), w, sizeof(hdr.w));
     s = check_sections(copy.data(), nwords);
     if (s != PHOBIC_OK) return s;
   }
@@ -550,8 +361,8 @@ extern "C" phobic_status phobic_deserialize(const void* h_buf, uint64_t bytes, v
   uint32_t flag = 0;
   if (on_device && e == hipSuccess) {
     uint32_t* d_flag = (uint32_t*)(h->d_image + nwords);
-    hipLaunchKernelGGL(k_check_clear, dim3(1), dim3(64), 0, st, d_flag);
-    hipLaunchKernelGGL(k_check_sections, dim3(1024), dim3(256), 0, st, h->d_image, d_flag);
+    hipLaunchKernelGGL(k_check_start, dim3(1), dim3(64), 0, st, h->d_image, hdr, d_flag);
+    hipLaunchKernelGGL(k_check_sections, dim3(1024), dim3(256), 0, st, h->d_image, hdr, d_flag);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipMemcpyAsync(&flag, d_flag, sizeof(flag), hipMemcpyDeviceToHost, st);
   }

@@ -1,0 +1,76 @@
+"""The checks of a loaded image, run on the CPU with every read of the device's part counted and checked.
+
+`tests/emu/image_check_emu.cpp` compiles the library's image_check.h with g++ and AddressSanitizer.  The
+images are the oracle's; whatever their words say, the device's part reads inside the image, and accepts
+only what the host's check accepts.
+"""
+
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2404_18497_amd import synth
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+HEADER = 24
+KINDS = {"rice": {}, "remap": dict(alpha=(99, 100)), "compact": dict(coding="compact"), "mixed": dict(n_compact=64)}
+
+
+@pytest.fixture(scope="module")
+def emu(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("g++ not available")
+    out = str(tmp_path_factory.mktemp("image") / "image_check_emu")
+    cmd = ["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address", "-Wno-attributes", "-I", os.path.join(HERE, "emu"),
+           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2404_18497_amd", "csrc"),
+           "-x", "c++", os.path.join(HERE, "emu", "image_check_emu.cpp"), "-o", out]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    return out
+
+
+@pytest.fixture(scope="module")
+def images():
+    keys = synth.u64_keys(60_000, 5)
+    return {k: oracle.build_u64(keys, oracle.params(lam=5.0, **kw), threads=8).image() for k, kw in KINDS.items()}
+
+
+def _check(emu, tmp_path, first, uploaded=None, threads=4096):
+    a, b = str(tmp_path / "a"), str(tmp_path / "b")
+    first.tofile(a)
+    (first if uploaded is None else uploaded).tofile(b)
+    r = subprocess.run([emu, str(threads), a, b], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-4000:]
+    keys = ("header", "fit", "bad", "host", "most", "all", "outside")
+    return dict(zip(keys, map(int, r.stdout.split())))
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_header_words(emu, images, tmp_path, kind):
+    # every header word altered: refused, or checked without a read outside the image
+    img = images[kind]
+    good = _check(emu, tmp_path, img)
+    assert good["header"] and good["fit"] and good["bad"] == 0 and good["host"] and good["outside"] == 0
+    for word in range(HEADER):
+        v = int(img[word])
+        for x in {0, 1, v + 1, v - 1, 2 * v, v ^ (1 << 20), v ^ (1 << 40), v ^ (1 << 63), (1 << 64) - 1} - {v}:
+            bad = img.copy()
+            bad[word] = np.uint64(x & (1 << 64) - 1)
+            r = _check(emu, tmp_path, bad)
+            assert r["outside"] == 0, (word, x)
+            assert not (r["fit"] and r["bad"] == 0) or r["host"], (word, x)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_header_is_read_once(emu, images, tmp_path, kind):
+    # the caller's memory changes after its header was checked: the sections are still found by the checked one
+    img = images[kind]
+    up = img.copy()
+    up[:HEADER] = np.uint64(0x0123456789ABCDEF)
+    r = _check(emu, tmp_path, img, up)
+    assert r["outside"] == 0 and r["fit"] and r["bad"] == 0 and r["host"]
