@@ -128,16 +128,18 @@ inline phobic_status check_sections(const uint64_t* w, uint64_t nwords) {
   return PHOBIC_OK;
 }
 
-// The same checks on the device, thread tid of nt.  The header h is the one that check_header and
-// sections_fit have passed, never the uploaded words: the caller's memory may have changed between the two
-// reads of it.  The select entries are checked segment by segment: entry s names a set bit with exactly
+// The same checks on the device, thread tid of nt: returns whether it does not accept what it read.  The
+// header h is the one that check_header and sections_fit have passed, never the uploaded words: the caller's
+// memory may have changed between the two reads of it.  The select entries are checked segment by segment: entry s names a set bit with exactly
 // kSelBlock ones from there to the next entry's (the last one: the remaining ones to the end), and none
 // precede entry 0's, so by induction every entry names the one it should; the three distances follow from
-// the ones after it.  Bound: one pass over the image (0.25 B per key).
+// the ones after it.  A thread reads at most kSegmentWords words of a segment, so that entries out of order or
+// a stream with long gaps do not make a few threads read the whole stream: what it does not accept, the host
+// decides (256 ones of a Rice stream take 12 words on average).  Bound: one pass over the image (0.25 B per key).
+constexpr uint64_t kSegmentWords = 256;
 struct ImageHeader {
   uint64_t w[kHeaderWords];
 };
-enum : uint32_t { kBadOffsets, kBadEncoders, kBadUnary, kBadSelect, kBadRemap };
 
 // width <= 64 bits at bit pos of the section that starts at word `sec`
 template <typename Words>
@@ -151,43 +153,44 @@ __device__ __forceinline__ uint64_t section_bits(const Words& w, uint64_t sec, u
 }
 
 template <typename Words>
-__device__ __forceinline__ uint32_t check_part(const Words& w, const ImageHeader& h, uint64_t tid, uint64_t nt) {
+__device__ __forceinline__ bool check_part(const Words& w, const ImageHeader& h, uint64_t tid, uint64_t nt) {
   const uint64_t n = h.w[kHN], K = h.w[kHK], B = h.w[kHB], total = h.w[kHTotal], R = h.w[kHR], dmin = h.w[kHDmin];
   const uint64_t sd = h.w[kHSecData], su = h.w[kHSecUnary], ss = h.w[kHSecSel];
   const uint32_t woff = (uint32_t)h.w[kHWoff];
-  uint32_t bad = 0;
+  bool bad = false;
   for (uint64_t j = tid; j <= K; j += nt) {
     const uint64_t o = expected_offset(j, R) + dmin + section_bits(w, h.w[kHSecOff], j * woff, woff);
     if (j == 0 ? o != 0
                : o < expected_offset(j - 1, R) + dmin + section_bits(w, h.w[kHSecOff], (j - 1) * woff, woff))
-      bad |= 1u << kBadOffsets;
-    if (j == K && o != total) bad |= 1u << kBadOffsets;
+      bad = true;
+    if (j == K && o != total) bad = true;
   }
   const uint64_t data_bits = (su - sd - 1) * 64;
   for (uint64_t i = tid; i < B; i += nt) {
     const uint64_t e = w[h.w[kHSecEnc] + i];
     const uint32_t wd = (uint32_t)(e & 0xFF);
-    if (wd > 32 || (e >> 8) + (uint64_t)wd * K > data_bits) bad |= 1u << kBadEncoders;
+    if (wd > 32 || (e >> 8) + (uint64_t)wd * K > data_bits) bad = true;
   }
   if ((h.w[kHCoding] & 0xFF) == PHOBIC_IC_RICE) {
     const uint64_t nvals = K * (B - h.w[kHNcompact]), nsel = (nvals + kSelBlock - 1) / kSelBlock;
     const uint64_t U = (h.w[kHUbits] + 63) / 64, ubits = U * 64;
-    if (tid == 0 && w[su + U] != 0) bad |= 1u << kBadUnary;
+    if (tid == 0 && w[su + U] != 0) bad = true;
     if (nsel == 0)
       for (uint64_t x = tid; x < U; x += nt)
-        if (w[su + x]) bad |= 1u << kBadUnary;
+        if (w[su + x]) bad = true;
     for (uint64_t s = tid; s < nsel; s += nt) {
       const uint64_t entry = w[ss + s], a = entry & 0xFFFFFFFFULL;
       const uint64_t end = s + 1 < nsel ? w[ss + s + 1] & 0xFFFFFFFFULL : ubits;
       const uint64_t want = s + 1 < nsel ? kSelBlock : nvals - s * kSelBlock;
-      if (a >= ubits || end <= a || end > ubits || !((w[su + (a >> 6)] >> (a & 63)) & 1)) {
-        bad |= 1u << kBadSelect;
+      if (a >= ubits || end <= a || end > ubits || ((end - 1) >> 6) - (a >> 6) >= kSegmentWords ||
+          (s == 0 && a >> 6 >= kSegmentWords) || !((w[su + (a >> 6)] >> (a & 63)) & 1)) {
+        bad = true;
         continue;
       }
       if (s == 0) {
         uint64_t before = w[su + (a >> 6)] & ((1ULL << (a & 63)) - 1);
         for (uint64_t x = 0; x < a >> 6; x++) before |= w[su + x];
-        if (before) bad |= 1u << kBadSelect;
+        if (before) bad = true;
       }
       uint64_t word = a >> 6, x = w[su + word] & (~0ULL << (a & 63)), seen = 0, out = a;
       uint32_t k = 1;  // the next distance: one number kSelSub k from the entry's on
@@ -200,16 +203,16 @@ __device__ __forceinline__ uint32_t check_part(const Words& w, const ImageHeader
           out |= (rel < kSelRelNone ? rel : kSelRelNone) << (32 + 10 * (k - 1));
         }
         seen += c;
-        if (last) break;
+        if (last || seen > want) break;
       }
-      if (seen != want) bad |= 1u << kBadUnary;
-      if (out != entry) bad |= 1u << kBadSelect;
+      if (seen != want) bad = true;
+      if (out != entry) bad = true;
     }
   }
   const uint64_t nremap = total - n;
   const uint32_t wr = (uint32_t)h.w[kHWremap];
   for (uint64_t g = tid; g < nremap; g += nt)
-    if (section_bits(w, h.w[kHSecRemap], g * wr, wr) >= n) bad |= 1u << kBadRemap;
+    if (section_bits(w, h.w[kHSecRemap], g * wr, wr) >= n) bad = true;
   return bad;
 }
 

@@ -14,6 +14,7 @@ import pytest
 
 import oracle
 from paper_2404_18497_amd import synth
+from synth_images import long_gap, swapped_select
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -74,3 +75,24 @@ def test_header_is_read_once(emu, images, tmp_path, kind):
     up[:HEADER] = np.uint64(0x0123456789ABCDEF)
     r = _check(emu, tmp_path, img, up)
     assert r["outside"] == 0 and r["fit"] and r["bad"] == 0 and r["host"]
+
+
+def test_select_entries_out_of_order(emu, tmp_path):
+    # refused, and no thread walks the stream for it: a thread reads a segment's share of it at most
+    img = oracle.build_u64(synth.u64_keys(400_000, 6), oracle.params(lam=5.0), threads=8).image()
+    nsel = int(img[17] - img[16]) - 1
+    good = _check(emu, tmp_path, img)
+    assert good["bad"] == 0 and nsel < 4096
+    r = _check(emu, tmp_path, swapped_select(img))
+    assert r["bad"] and not r["host"] and r["outside"] == 0
+    assert r["most"] <= 2 * 256 and r["all"] <= 2 * good["all"]
+
+
+@pytest.mark.parametrize("at", [0, 1, 300])
+def test_long_gaps_are_left_to_the_host(emu, images, tmp_path, at):
+    # a gap of 200 words stays within the words a thread reads of a segment, one of 2000 does not
+    img = long_gap(images["rice"], at, 200)
+    r = _check(emu, tmp_path, img)
+    assert r["fit"] and r["host"] and r["bad"] == 0
+    r = _check(emu, tmp_path, long_gap(images["rice"], at, 2000))
+    assert r["fit"] and r["host"] and r["bad"] and r["most"] <= 2 * 256 and r["outside"] == 0
