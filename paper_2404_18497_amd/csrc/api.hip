@@ -256,10 +256,6 @@ __global__ __launch_bounds__(256) void k_check_sections(const uint64_t* __restri
     atomicOr(flag, 1u);
 }
 
-// Images of fewer words are checked on the host, at about 4.5 ns a word (8900 words: 55 us a load); the
-// device's check and the round trip for its answer take 47 us at 16 500 words and 58 us at 57 000.
-constexpr uint64_t kDeviceCheckWords = 1 << 13;
-
 }  // namespace phobic
 
 using namespace phobic;
@@ -323,7 +319,7 @@ extern "C" phobic_status phobic_deserialize(const void* h_buf, uint64_t bytes, v
   const uint64_t* const w = hdr.w;
   phobic_status s = check_header(w, nwords);
   if (s != PHOBIC_OK) return s;
-  const bool on_device = nwords >= kDeviceCheckWords && sections_fit(w, nwords);
+  const bool on_device = check_on_device(w, nwords);
   std::vector<uint64_t> copy;
   if (!on_device) {
     copy.resize(nwords);

@@ -230,4 +230,23 @@ inline bool sections_fit(const uint64_t* w, uint64_t nwords) {
          ss + (K * (B - w[kHNcompact]) + kSelBlock - 1) / kSelBlock + 1 == sr;
 }
 
+// Whether the sections of an image are checked on the device rather than on the host: a second launch and the
+// wait for its answer cost 12 to 20 us a load, so the host keeps the check while it takes less.  It takes
+// about 0.15 ns per value of the Rice encoders (the unary stream and its select entries; Compact images have
+// neither), 0.6 ns per remap entry, 1 ns per offset and encoder word and 0.07 ns per word of its copy, and
+// from 2^17 words on the copy alone (pages mapped anew) costs as much as the device's check.  A load and its
+// first 1000 lookups, us, host / device:
+//   Rice, lambda 7: 14 571 words 58 / 69, 28 719 77 / 75, 57 090 110 / 85, 284 010 621 / 158
+//   Rice, lambda 5: 9914 55 / 68, 16 153 62 / 69, 31 829 85 / 74, 63 091 126 / 84
+//   Compact, lambda 7: 10 018 45 / 64, 33 517 58 / 69, 67 573 71 / 81, 136 411 145 / 121, 345 386 234 / 157
+//   300 of 358 encoders Compact: 32 544 59 / 75, 65 487 78 / 84, 131 883 158 / 125
+//   Compact, alpha 0.9: 11 884 57 / 63, 18 233 67 / 64, 30 363 84 / 68; alpha 0.99: 35 635 62 / 70, 72 171 86 / 81
+inline bool check_on_device(const uint64_t* w, uint64_t nwords) {
+  if (!sections_fit(w, nwords)) return false;
+  const uint64_t rice = (w[kHCoding] & 0xFF) == PHOBIC_IC_RICE ? w[kHK] * (w[kHB] - w[kHNcompact]) : 0;
+  const double host_ns = 0.15 * (double)rice + 0.6 * (double)(w[kHTotal] - w[kHN]) + (double)(w[kHK] + w[kHB]) +
+                         0.07 * (double)nwords;
+  return nwords >= 1 << 17 || host_ns > 17000;
+}
+
 }  // namespace phobic

@@ -5,7 +5,7 @@
 // Usage: image_check_emu THREADS IMAGE UPLOADED: IMAGE holds the words as first read (whose header is
 // checked), UPLOADED those that reached the device.  Prints: header accepted, sections fit, device verdict
 // (0: accepted), host accepts the uploaded words under the checked header, most reads of one thread, all
-// reads, reads out of range.
+// reads, reads out of range, whether a load has the device check the sections.
 #include <hip/hip_runtime.h>
 
 #include "image_check.h"
@@ -66,7 +66,8 @@ int main(int argc, char** argv) {
     std::memcpy(up.data(), h.w, sizeof(h.w));
     host = check_sections(up.data(), up.size()) == PHOBIC_OK;
   }
-  std::printf("%d %d %u %d %llu %llu %llu\n", (int)header, (int)fit, bad, (int)host, (unsigned long long)most,
-              (unsigned long long)all, (unsigned long long)outside);
+  std::printf("%d %d %u %d %llu %llu %llu %d\n", (int)header, (int)fit, bad, (int)host, (unsigned long long)most,
+              (unsigned long long)all, (unsigned long long)outside,
+              (int)(header && check_on_device(h.w, up.size())));
   return 0;
 }

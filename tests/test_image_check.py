@@ -47,7 +47,7 @@ def _check(emu, tmp_path, first, uploaded=None, threads=4096):
     (first if uploaded is None else uploaded).tofile(b)
     r = subprocess.run([emu, str(threads), a, b], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr[-4000:]
-    keys = ("header", "fit", "bad", "host", "most", "all", "outside")
+    keys = ("header", "fit", "bad", "host", "most", "all", "outside", "device")
     return dict(zip(keys, map(int, r.stdout.split())))
 
 
@@ -96,3 +96,15 @@ def test_long_gaps_are_left_to_the_host(emu, images, tmp_path, at):
     assert r["fit"] and r["host"] and r["bad"] == 0
     r = _check(emu, tmp_path, long_gap(images["rice"], at, 2000))
     assert r["fit"] and r["host"] and r["bad"] and r["most"] <= 2 * 256 and r["outside"] == 0
+
+
+@pytest.mark.parametrize("n,kw,device", [
+    (300_000, dict(coding="compact"), False),  # the host reads the offsets and encoders alone
+    (300_000, {}, False), (700_000, {}, True),  # 10 000 and 22 000 words with a unary stream
+    (300_000, dict(n_compact=490), False),
+    (200_000, dict(coding="compact", alpha=(9, 10)), False), (500_000, dict(coding="compact", alpha=(9, 10)), True),
+])
+def test_the_checker_follows_the_work(emu, tmp_path, n, kw, device):
+    img = oracle.build_u64(synth.u64_keys(n, 7), oracle.params(lam=5.0, **kw), threads=8).image()
+    assert img.size > 1 << 12
+    assert _check(emu, tmp_path, img)["device"] == device
