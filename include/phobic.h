@@ -166,16 +166,21 @@ phobic_status phobic_partition_u64(const uint64_t* d_keys, uint64_t n, const pho
 /* Launch shape of the pilot search: waves_per_group wavefronts per workgroup, each working on one
  * partition at a time; with groups_per_cu > 0 the search runs persistently (groups_per_cu
  * workgroups per compute unit pulling items_per_grab partitions at a time from an atomic queue),
- * with 0 it launches one wavefront per partition.  The shape never changes a result. */
+ * with 0 it launches one wavefront per partition.  With `reserved` set to PHOBIC_SEARCH_TEAMS the shape
+ * is that of builds with partitions enough to fill the device; builds with fewer give each partition a
+ * team of 4 to 16 wavefronts, by a rule on their number and bucket size.  Any other value of `reserved`
+ * means 0: the shape as it stands for every build.  Neither ever changes a result. */
+#define PHOBIC_SEARCH_TEAMS 1
 typedef struct {
   uint32_t waves_per_group; /* 1, 2, 4 or 8 */
   uint32_t groups_per_cu;   /* 0 = one wavefront per partition; else persistent */
   uint32_t items_per_grab;  /* partitions taken per queue access (persistent mode), >= 1 */
-  uint32_t reserved;
+  uint32_t reserved;        /* PHOBIC_SEARCH_TEAMS or 0 */
 } phobic_search_config;
 
 /* Sets the search shape used by later builds on the calling process (all devices).  The default is
- * one wavefront per workgroup, one wavefront per partition ({1, 0, 1, 0}). */
+ * one wavefront per workgroup, one wavefront per partition, and teams for builds of few partitions
+ * ({1, 0, 1, PHOBIC_SEARCH_TEAMS}). */
 phobic_status phobic_set_search_config(const phobic_search_config* cfg);
 phobic_status phobic_get_search_config(phobic_search_config* out);
 

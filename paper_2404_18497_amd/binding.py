@@ -401,16 +401,19 @@ class Server:
     __del__ = close
 
 
-def set_search_config(waves_per_group=4, groups_per_cu=0, items_per_grab=1):
-    cfg = SearchConfig(waves_per_group, groups_per_cu, items_per_grab, 0)
+def set_search_config(waves_per_group=4, groups_per_cu=0, items_per_grab=1, teams=False):
+    """Sets the search's launch shape for later builds of this process. teams=True (the default before any
+    call): builds of few partitions give each a team of wavefronts, and the shape governs the others."""
+    cfg = SearchConfig(waves_per_group, groups_per_cu, items_per_grab, int(bool(teams)))
     _check(lib().phobic_set_search_config(C.byref(cfg)))
 
 
 def get_search_config() -> dict:
     cfg = SearchConfig()
     _check(lib().phobic_get_search_config(C.byref(cfg)))
-    return {"waves_per_group": cfg.waves_per_group, "groups_per_cu": cfg.groups_per_cu,
-            "items_per_grab": cfg.items_per_grab}
+    shape = {"waves_per_group": cfg.waves_per_group, "groups_per_cu": cfg.groups_per_cu,
+             "items_per_grab": cfg.items_per_grab}
+    return shape | {"teams": True} if cfg.reserved else shape
 
 
 def deserialize(image: np.ndarray, stream=None) -> MPHF:

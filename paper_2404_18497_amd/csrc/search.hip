@@ -926,7 +926,7 @@ __global__ __launch_bounds__(64 * kTeamMaxWaves) void k_search_team(SearchArgs a
 // Search launch shape
 // ---------------------------------------------------------------------------------------------
 std::mutex g_cfg_mu;
-phobic_search_config g_cfg = {1, 0, 1, 0};  // one partition per workgroup
+phobic_search_config g_cfg = {1, 0, 1, PHOBIC_SEARCH_TEAMS};  // one partition per workgroup
 
 phobic_search_config search_config() {
   std::lock_guard<std::mutex> lock(g_cfg_mu);
@@ -994,7 +994,7 @@ hipError_t launch_team(SearchArgs& sa, uint64_t items, uint32_t W, size_t lds, h
   return hipGetLastError();
 }
 
-// Wavefronts per partition under the default shape (1: the one-wavefront kernels).  A team pays while the
+// Wavefronts per partition where teams are allowed (1: the one-wavefront kernels).  A team pays while the
 // launch leaves wavefront slots empty, and longer the more pilots a bucket tries (keys per bucket,
 // lambda): it issues 1.5 to 3 times the instructions per partition.  A CU holds three teams of eight
 // or six of four (77 registers), of the kMany variant two and four (104).  Search times in us, P = 2500,
@@ -1045,9 +1045,10 @@ bool team_many(const SearchArgs& sa, uint64_t items) {
   return (items <= sa.cus && sa.bucket_keys >= 8.8f) || (items <= 3ull * sa.cus && sa.bucket_keys >= 9.8f);
 }
 
-// The wavefronts per partition of the launch: teams under the default shape, as many as fit the LDS.
+// The wavefronts per partition of the launch: teams if the configuration allows them, as many as fit the
+// LDS.  Its shape governs the launches that the rule gives one wavefront per partition.
 uint32_t team_size(SearchArgs& sa, uint64_t items, const phobic_search_config& cfg) {
-  uint32_t W = cfg.waves_per_group == 1 && cfg.groups_per_cu == 0 ? team_waves(sa, items) : 1;
+  uint32_t W = cfg.reserved == PHOBIC_SEARCH_TEAMS ? team_waves(sa, items) : 1;
   while (W > 1 && size_team_lds(sa, W) > sa.lds_limit) W /= 2;
   return W;
 }
@@ -1094,7 +1095,7 @@ extern "C" phobic_status phobic_set_search_config(const phobic_search_config* cf
     return fail(PHOBIC_E_INVALID, "items_per_grab must be in [1, 4096]");
   std::lock_guard<std::mutex> lock(g_cfg_mu);
   g_cfg = *cfg;
-  g_cfg.reserved = 0;
+  if (g_cfg.reserved != PHOBIC_SEARCH_TEAMS) g_cfg.reserved = 0;
   return PHOBIC_OK;
 }
 
