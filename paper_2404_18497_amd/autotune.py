@@ -5,7 +5,9 @@ workgroup, and either one wavefront per partition or a persistent grid of `group
 workgroups per compute unit pulling `items_per_grab` partitions at a time from an atomic queue --
 changes only speed, never a result. The tuner times the search phase of real builds for every
 candidate shape (best of `repeats`), installs the fastest with ``set_search_config`` and returns the
-full table so callers can record it.
+full table so callers can record it. Unless a candidate says otherwise it allows teams: builds of few
+partitions keep theirs, whose launch no shape changes, so that a shape tuned on a large batch does not
+slow the small builds of the process.
 """
 
 from __future__ import annotations
@@ -38,7 +40,7 @@ def tune(build, repeats: int = 2, cands=None, install: bool = True, log=None):
     """Times `build()` (returning a handle or a list of batch handles) under every candidate shape.
 
     Returns (best_shape, [(shape, search_ms), ...]); installs the best shape unless install=False."""
-    cands = cands or candidates()
+    cands = [{"teams": True, **c} for c in cands or candidates()]
     before = binding.get_search_config()
     table = []
     try:

@@ -1,12 +1,12 @@
 """The search's launch shape and whether builds of few partitions get teams: what is set is what holds,
-and reading and setting back changes nothing."""
+reading and setting back changes nothing, and tuning on a large batch leaves the teams of small builds."""
 
 import ctypes as C
 
 import numpy as np
 import pytest
 
-from paper_2404_18497_amd import binding, synth
+from paper_2404_18497_amd import autotune, binding, synth
 
 TEAMS = 1
 
@@ -40,6 +40,22 @@ def test_default_and_explicit_shapes():
     _set(2, 0, 1, 7)  # values without a meaning are taken as 0
     assert _reserved() == 0
     binding.set_search_config(waves_per_group=8, groups_per_cu=4)
+    assert _reserved() == 0
+
+
+@pytest.mark.parametrize("cands", [None, [dict(waves_per_group=8, groups_per_cu=4, items_per_grab=1)]])
+def test_tuning_keeps_the_teams(cands):
+    class Built:
+        def build_info(self):
+            return {"search_ms": 1.0 if binding.get_search_config()["waves_per_group"] == 8 else 2.0}
+
+        def close(self):
+            pass
+
+    best, table = autotune.tune(lambda: [Built()], repeats=1, cands=cands)
+    assert best["waves_per_group"] == 8 and len(table) == (1 if cands else len(autotune.candidates()))
+    assert binding.get_search_config() == best and _reserved() == TEAMS
+    autotune.tune(lambda: [Built()], repeats=1, cands=[dict(waves_per_group=8, teams=False)])
     assert _reserved() == 0
 
 
