@@ -38,6 +38,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -152,6 +153,24 @@ def measured_traffic(kernel: str, n: int, lam: float):
     return rec["read_bytes"] + rec["write_bytes"]
 
 
+def search_kernel_name(cfg, partitions, cus):
+    """The search kernel of a build with partitions of about 2500 keys (tables below 4096 slots: the one-pass
+    scan instance), or None where the launch rule may give the partitions teams of wavefronts instead."""
+    if cfg.get("teams") and partitions <= 64 * cus:
+        return None
+    return (f"k_search_persistent<{cfg['waves_per_group']}, false>" if cfg["groups_per_cu"]
+            else f"k_search<{cfg['waves_per_group']}, false>")
+
+
+def query_kernel_name(lookups, buckets):
+    """The kernel of one phobic_query_u64 call, by its lookups and the buckets per partition."""
+    if lookups <= 1 << 19:
+        return "k_query_few"
+    if lookups <= 1 << 24:
+        return "k_query_mid"
+    return "k_query_u64<true>" if buckets <= 1024 else "k_query_u64<false>"
+
+
 def _timed(torch, build, queries, steps, warmup):
     """Runs `warmup` untimed and `steps` timed steps of build() followed by queries(handle); returns
     (ms per step by the host clock around the synchronized timed region, mean build ms and mean query
@@ -239,9 +258,7 @@ def headline(args):
 
     # dominant kernel and its roofline (per launch; durations from HIP events on the launch stream)
     cfg = binding.get_search_config()
-    # tables of P 2500 partitions stay below 4096 slots: the one-pass scan instance
-    search_kernel = (f"k_search_persistent<{cfg['waves_per_group']}, false>" if cfg["groups_per_cu"]
-                     else f"k_search<{cfg['waves_per_group']}, false>")
+    search_kernel = search_kernel_name(cfg, -(-n // 2500), torch.cuda.get_device_properties(0).multi_processor_count)
     per_step = {"k_search": phase["search_ms"], "k_query_u64": query_ms}
     dom = max(per_step, key=per_step.get)
     if dom == "k_search":
@@ -258,8 +275,7 @@ def headline(args):
     else:
         per = query_ms / nlaunch
         achieved = 16.0 * min(batch, n) / (per * 1e-3) / 1e9
-        # the query instance of calls of 2^19 to 2^24 lookups
-        qkernel = "k_query_mid"
+        qkernel = query_kernel_name(min(batch, n), math.ceil(2500 / args.lam))
         roofline = {"kernel": qkernel, "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                     "traffic": measured_traffic(qkernel, n, args.lam),
