@@ -999,28 +999,36 @@ hipError_t launch_team(SearchArgs& sa, uint64_t items, uint32_t W, size_t lds, h
 // lambda): it issues 1.5 to 3 times the instructions per partition.  A CU holds three teams of eight
 // or six of four (77 registers), of the kMany variant two and four (104).  Search times in us, P = 2500,
 // one wavefront / 4 / 8 / 16 per partition (many: the kMany variant):
-//   lambda 5:  160 partitions 457/284/218/233, 520: 631/365/331/575, 1500: 491/497/613/1189, 3000: 533/908
+//   lambda 5:  160 partitions 457/284/218/233, 520: 631/365/331/575
 //   lambda 7:  1: 451/252/225/266, 160: 591/321/305/360 (many -/363/325/382), 520: 711/413/386/767,
-//              1000: 830/459/616/1177, 2000: 921/758/1018, 3000: 1291/1024/1455, 4000: 941/1646
+//              1000: 830/459/616/1177
 //   lambda 9:  160: 1934/829/692/769 (many -/827/642/659), 520: 2248/986/909/1721 (many -/1037/1008/1588),
-//              1000: 2432/1089/1329/2621, 2000: 3458/1949/2322, 3000: 3461/2417/3335, 4000: 2680/2883/4018
+//              1000: 2432/1089/1329/2621
 //   lambda 10: 160: 5082/1770/1323/1332 (many -/1531/1085/1000), 520: 6500/2473/1865 (many -/2155/1624/2260)
 //   lambda 10.5: 160: 9039/2703/1919/1788 (many -/2448/1568/1329), 520: many 2172 against 2544 at eight
-//   lambda 11: 8000: 22738/20062/24754
 //   lambda 12: 160: 38796/9310/5955/4856 (many -/9569/5640/4222), 520: 51465/13386/8484/8471 (many
-//              -/14696/9100/6499), 1000: 53308/12325/9443/12746 (many 10511 and 10374), 2000:
-//              50323/17567/16381/26222, 4000: 52056/27472/28338, 16000: 106844/86692/99983,
-//              40 000: 175300/205800/242200
+//              -/14696/9100/6499), 1000: 53308/12325/9443/12746 (many 10511 and 10374), 2000: 50323/17567/16381/26222
 //   lambda 7, larger P: 10 000 (100 partitions) 1622/1025/781/764, (1000) 1855/1404/1632/2762;
 //              20 000 (500) 2579/2157/1744/2478; 50 000 (200) 6008/4475/3236/2888; 100 000 (100)
 //              11923/8660/6366/5641
+// Beyond three partitions per CU the one-wavefront time depends on the keys: it is that of the costliest
+// partitions, while a team's launch is bound by the work of all.  Lines are drawn where the fastest of five
+// to seven key sets still gains.  One wavefront, fastest to slowest key set / teams of four, us:
+//   P 2500:  lambda 7: 1537 partitions 778-1291/597-738, 1800: 777-962/715-766, 2200: 730-970/798-838, 3072: 809-1205/
+//            1004-1042; lambda 8: 1800 1172-1641/1043-1111, 2200 1123-2226/1114-1260, 3072 1171-1897/1438-1458;
+//            lambda 9: 2200 2310-2954/1906-2078, 2600 2424-3308/2097-2234; lambda 9.8: 3072 5189-5588/3928-4184;
+//            lambda 5: 1200 479-610/439-465, 1536 506-718/499-518; lambda 4: 1200 486-644/463-494, 1536 490-597/529-541;
+//            lambda 3: 1000 509-522/443-450, 1536 535-544/575-584
+//   lambda 7: P 1000: 3072 710-935/562-587; P 1500: 2200 657-1112/569-620, 3072 627-1223/728-748; P 3000: 1537 772-959/
+//            736-773, 1800 797-974/855-888, 3072 840-1458/1219-1259; P 4000: 1537 939-1132/917-952, 1800 972-1053/1098-1159
+//   where the LDS holds only 1280 teams of four: P 5000, lambda 7: 1280 1096-1159/1004-1015, 1400 1105-1196/1242-1311;
+//            lambda 9: 1280 3721-4132/2693-2934, 1600 3954-4218/3548-3732
+//   P 2500, lambda 10.1: 4096 7508-9099/6259-6726; lambda 10.9: 6000 16014-22614/14822-15571, 8192 19571-23061/19602-19984;
+//            lambda 11.9: 12 000 70919-82771/61130-64129.  At P 3000 the windows of two seeds leave a quarter of a part's
+//            lanes idle: 10.9: 6000 17175-20566/18985-19879, 4096 15173-19107/13940-14480; 11.9: 12 000 68962-76188/78291-80281
 // Larger tables (more than 8192 slots) take the most wavefronts with which every partition has its team at
 // once: their bitmaps and position buffers leave few teams per CU, and with 2000 partitions of 50 000
 // teams of four took 20.1 ms where one wavefront each takes 12.7 (300 of them: 4.08 against 6.17 ms).
-// For the same reason more than six partitions per CU need, where the LDS and not the registers limits the
-// teams, room for most of them: 1750 partitions of 4000 keys (1280 teams at once) take 1084 us against
-// 1170 and 1285 of 7000 keys at lambda 9 (1024) 3451 against 4123, but 2400 of 5000 keys (1280) 1781
-// against 1141 and at lambda 9 4710 against 3983.
 uint32_t team_waves(SearchArgs& sa, uint64_t items) {
   const uint64_t c = sa.cus;
   const float l = sa.bucket_keys;
@@ -1030,12 +1038,27 @@ uint32_t team_waves(SearchArgs& sa, uint64_t items) {
   if (sa.max_m > kTeamScratchBits) return items <= teams(16) ? 16 : (items <= teams(8) ? 8 : (items <= teams(4) ? 4 : 1));
   if (items <= c) return l >= 9.8f ? 16 : 8;
   if (items <= 3 * c) return l >= 11.5f ? 16 : 8;
-  if (items <= 6 * c) return l >= 10.8f ? 8 : 4;
-  if (items <= 12 * c) return l >= 6.0f && (teams(4) == 6 * c || 5 * items <= 7 * teams(4)) ? 4 : 1;
+  if (items <= 6 * c && l >= 10.8f) return 8;
+  if (items <= 12 * c) {
+    const uint64_t at_once = teams(4);  // 6 c unless the LDS limits it: then a second, nearly empty turn
+    if (at_once < 6 * c && (l < 8.8f ? items > at_once : 5 * items > (l < 9.7f ? 6 : 7) * at_once)) return 1;
+    if (l >= 9.7f) return 4;
+    if (items > 6 * c && l < 6.0f) return 1;
+    // where the work of all partitions (items p) takes as long as one partition (its keys p, and a constant)
+    const float s = l < 3.6f   ? 0.3f
+                    : l < 4.6f ? 0.55f
+                    : l < 6.4f ? 0.8f
+                    : l < 8.3f ? 1.0f
+                    : l < 8.8f ? 1.1f
+                    : l < 9.25f ? 1.25f
+                                : 1.6f;
+    return (float)items <= s * (4.3f + 6850.0f / (l * (float)sa.B)) * (float)c ? 4 : 1;
+  }
   if (sa.max_m > 4096) return 1;
-  if (items <= 16 * c) return l >= 10.0f ? 4 : 1;
-  if (items <= 32 * c) return l >= 10.8f ? 4 : 1;
-  return items <= 64 * c && l >= 11.8f ? 4 : 1;
+  const bool full = l * (float)sa.B <= 2700.0f;
+  if (items <= 16 * c) return l >= (full ? 10.0f : 10.8f) ? 4 : 1;
+  if (items <= 32 * c) return l >= (full ? 10.8f : 11.8f) ? 4 : 1;
+  return full && items <= 64 * c && l >= 11.8f ? 4 : 1;
 }
 
 // Whether the team is the kMany variant: with few partitions its registers cost no team its place, and
