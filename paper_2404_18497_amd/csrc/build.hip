@@ -1633,9 +1633,10 @@ struct WsBlock {
 struct Workspace {
   int device = 0;
   std::vector<WsBlock> dev, host;
+  uint64_t parts = 0;  // leased: partitions that its build searches
 };
 std::mutex g_ws_mu;
-std::vector<Workspace*> g_ws_idle;
+std::vector<Workspace*> g_ws_idle, g_ws_leased;
 
 Workspace* lease_workspace(int device) {
   std::lock_guard<std::mutex> lock(g_ws_mu);
@@ -1643,16 +1644,31 @@ Workspace* lease_workspace(int device) {
     if (g_ws_idle[i]->device == device) {
       Workspace* w = g_ws_idle[i];
       g_ws_idle.erase(g_ws_idle.begin() + (ptrdiff_t)i);
+      g_ws_leased.push_back(w);
       return w;
     }
   }
   Workspace* w = new Workspace();
   w->device = device;
+  g_ws_leased.push_back(w);
   return w;
+}
+
+// Partitions that the builds in flight on w's device search beside w's `parts` and with them, each other
+// build counted with `parts` at most: what the search's launch rule takes the device to be filled with.
+uint64_t search_load(Workspace* w, uint64_t parts) {
+  std::lock_guard<std::mutex> lock(g_ws_mu);
+  w->parts = parts;
+  uint64_t load = 0;
+  for (const Workspace* o : g_ws_leased)
+    if (o->device == w->device) load += std::min(o->parts, parts);
+  return load;
 }
 
 void return_workspace(Workspace* w) {
   std::lock_guard<std::mutex> lock(g_ws_mu);
+  w->parts = 0;
+  g_ws_leased.erase(std::find(g_ws_leased.begin(), g_ws_leased.end(), w));
   g_ws_idle.push_back(w);
 }
 
@@ -1686,6 +1702,7 @@ struct Scratch {
     (void)hipGetDevice(&d);
     ws = lease_workspace(d);
   }
+  uint64_t load(uint64_t parts) { return search_load(ws, parts); }
   template <class T>
   hipError_t get(T** p, uint64_t count) {
     void* q = nullptr;
@@ -1783,14 +1800,16 @@ hipError_t spin_sync(hipStream_t st) {
   }
 }
 
-// What the launch rule of the search asks of the device, and the average bucket size.
-hipError_t search_device_limits(SearchArgs& sa, double bucket_keys) {
+// What the launch rule of the search asks of the device and of the builds in flight on it (at least this
+// build's partitions), and the average bucket size.
+hipError_t search_device_limits(SearchArgs& sa, double bucket_keys, uint64_t load) {
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   sa.cus = (uint32_t)cus;
   sa.lds_limit = (uint32_t)max_lds_per_group();
   sa.bucket_keys = (float)bucket_keys;
+  sa.load = load;
   return e;
 }
 
@@ -1864,6 +1883,7 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
   h->prm = prm;
 
   Scratch S(st);
+  if (!part_offsets_out) (void)S.load(K);  // builds beside this one see it from here on
   Timer tm(st);
   auto t_host0 = std::chrono::steady_clock::now();
   {
@@ -2156,7 +2176,7 @@ phobic_status build_impl(const BuildInput& in, const phobic_params* params, hipS
   const uint32_t mm = (uint32_t)std::max<uint64_t>(max_m, 1);
   const uint32_t mb = std::max<uint32_t>(hmaxb, 1);
   size_search_lds(sa, mm, mb, B, wide);
-  PHOBIC_HIP(search_device_limits(sa, (double)n / ((double)K * B)));
+  PHOBIC_HIP(search_device_limits(sa, (double)n / ((double)K * B), S.load(K)));
   if (wide && sa.wave_lds > max_lds_per_group())
     return fail(PHOBIC_E_CAPACITY, "a partition of " + std::to_string(mm) + " slots does not fit the LDS of one workgroup");
   sa.owner = nullptr;
@@ -2781,6 +2801,7 @@ phobic_status build_batch_impl(const uint64_t* const* keys, const uint64_t* coun
   }
 
   Scratch S(st);
+  (void)S.load(Ktot);
   Timer tm(st);
   auto t_host0 = std::chrono::steady_clock::now();
   BatchDesc* d_desc;
@@ -2859,7 +2880,7 @@ phobic_status build_batch_impl(const uint64_t* const* keys, const uint64_t* coun
   sa.B = B;
   const uint32_t mm = std::max<uint32_t>(hinfo[2], 1), mb = std::max<uint32_t>(hinfo[1], 1);
   size_search_lds(sa, mm, mb, B, false);
-  PHOBIC_HIP(search_device_limits(sa, (double)Ntot / ((double)Ktot * B)));
+  PHOBIC_HIP(search_device_limits(sa, (double)Ntot / ((double)Ktot * B), S.load(Ktot)));
   sa.owner = owner;
   sa.Kbase = d_Kbase;
   sa.Kt = d_Kt;

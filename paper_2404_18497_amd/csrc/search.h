@@ -46,6 +46,7 @@ struct SearchArgs {
   uint32_t grab;
   unsigned long long* fail_part;  // non-null: receives the lowest failing partition index (atomic min)
   const uint32_t* order;          // non-null: the launch takes partitions in this order (one MPHF)
+  uint64_t load;                  // partitions of this and other builds in flight (search_load), for the launch rule
 };
 
 // Launches the search over `items` partitions (sa.K of them in the partition index space) on the

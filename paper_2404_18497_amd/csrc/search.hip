@@ -1068,10 +1068,12 @@ bool team_many(const SearchArgs& sa, uint64_t items) {
   return (items <= sa.cus && sa.bucket_keys >= 8.8f) || (items <= 3ull * sa.cus && sa.bucket_keys >= 9.8f);
 }
 
-// The wavefronts per partition of the launch: teams if the configuration allows them, as many as fit the
-// LDS.  Its shape governs the launches that the rule gives one wavefront per partition.
+// The wavefronts per partition of the launch: teams if the configuration allows them, by the partitions in
+// flight on the device (other builds fill its idle slots as well as more partitions would: eight threads that
+// each build 1600 partitions at lambda 7 took 387 us a build without teams, 573 with teams by their own
+// count), as many as fit the LDS.  Its shape governs the launches that the rule gives one wavefront per partition.
 uint32_t team_size(SearchArgs& sa, uint64_t items, const phobic_search_config& cfg) {
-  uint32_t W = cfg.reserved == PHOBIC_SEARCH_TEAMS ? team_waves(sa, items) : 1;
+  uint32_t W = cfg.reserved == PHOBIC_SEARCH_TEAMS ? team_waves(sa, std::max(sa.load, items)) : 1;
   while (W > 1 && size_team_lds(sa, W) > sa.lds_limit) W /= 2;
   return W;
 }
@@ -1079,8 +1081,8 @@ uint32_t team_size(SearchArgs& sa, uint64_t items, const phobic_search_config& c
 bool search_holds_all(SearchArgs& sa, uint64_t items) {
   const uint32_t W = team_size(sa, items, search_config());
   if (W == 1) return false;
-  const uint32_t waves = team_many(sa, items) ? 16 : 24;  // of the kernel, per CU
-  return items <= std::min<uint64_t>(waves / W, sa.lds_limit / size_team_lds(sa, W)) * sa.cus;
+  const uint32_t waves = team_many(sa, std::max(sa.load, items)) ? 16 : 24;  // of the kernel, per CU
+  return std::max(sa.load, items) <= std::min<uint64_t>(waves / W, sa.lds_limit / size_team_lds(sa, W)) * sa.cus;
 }
 
 hipError_t launch_search(SearchArgs& sa, uint64_t items, hipStream_t st, unsigned long long* queue) {
@@ -1089,7 +1091,7 @@ hipError_t launch_search(SearchArgs& sa, uint64_t items, hipStream_t st, unsigne
   if (W > 1) {
     const size_t lds = size_team_lds(sa, W);
     if (sa.max_m <= kTeamScratchBits)
-      return team_many(sa, items) ? launch_team<true, true, true>(sa, items, W, lds, st)
+      return team_many(sa, std::max(sa.load, items)) ? launch_team<true, true, true>(sa, items, W, lds, st)
                                   : launch_team<true, true, false>(sa, items, W, lds, st);
     return sa.max_m < kTeamShiftSlots ? launch_team<true, false, false>(sa, items, W, lds, st)
                                       : launch_team<false, false, false>(sa, items, W, lds, st);

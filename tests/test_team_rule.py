@@ -28,15 +28,30 @@ def _largest_bucket(P, lam):
     return P * k / (len(T) - 1)
 
 
-def test_measured_cases(tmp_path):
+@pytest.fixture(scope="module")
+def rule(tmp_path_factory):
     if shutil.which("g++") is None:
         pytest.skip("g++ not available")
-    exe = str(tmp_path / "rule")
+    exe = str(tmp_path_factory.mktemp("rule") / "rule")
     cmd = ["g++", "-std=c++17", "-O1", "-Wno-attributes", "-I", os.path.join(HERE, "emu"),
            "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2404_18497_amd", "csrc"),
            f'-DSEARCH_SRC="{SEARCH_SRC}"', "-x", "c++", os.path.join(HERE, "emu", "team_rule_emu.cpp"), "-o", exe]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-4000:]
-    lines = "".join("%g %d %g %g\n" % (P, K, lam, _largest_bucket(P, lam)) for P, K, lam in CASES)
-    out = subprocess.run([exe], input=lines, capture_output=True, text=True, check=True).stdout.split()
-    assert dict(zip(CASES, map(int, out))) == CASES
+
+    def run(cases):  # (P, partitions, lambda, load)
+        lines = "".join("%g %d %g %g %d\n" % (P, K, lam, _largest_bucket(P, lam), load) for P, K, lam, load in cases)
+        out = subprocess.run([exe], input=lines, capture_output=True, text=True, check=True).stdout.split()
+        return list(map(int, out))
+
+    return run
+
+
+def test_measured_cases(rule):
+    out = rule([(P, K, lam, K) for P, K, lam in CASES])
+    assert dict(zip(CASES, out)) == CASES
+
+
+def test_builds_beside_each_other(rule):
+    # other builds in flight fill the device as more partitions would; alone, and where they leave it idle, teams
+    assert rule([(2500, 1600, 7.0, 1600), (2500, 1600, 7.0, 4 * 1600), (2500, 80, 7.0, 8 * 80), (2500, 1, 7.0, 8)]) == [4, 1, 8, 8]
