@@ -153,8 +153,8 @@ phobic_status phobic_serialize(const phobic_mphf* h, void* h_buf, uint64_t* inou
 
 /* Rebuilds a handle on the current device from an image made by phobic_serialize (the layout of
  * Sec. 4 and Sec. 4.1 written there).  Every field, section extent, unary stream and select entry is
- * checked first (header and small images on the host, the sections of larger ones on the device after
- * the upload); an inconsistent image gives PHOBIC_E_FORMAT and no handle. */
+ * checked first (the header on the host, the sections there or, where that would take longer, on the
+ * device after the upload); an inconsistent image gives PHOBIC_E_FORMAT and no handle. */
 phobic_status phobic_deserialize(const void* h_buf, uint64_t bytes, void* hip_stream, phobic_mphf** out);
 
 /* Hashing and partitioning alone, for parity checks: hashes and partitions the keys.  d_offsets gets K + 1

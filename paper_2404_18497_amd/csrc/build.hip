@@ -1206,10 +1206,10 @@ __device__ __forceinline__ void offset_stats(const uint64_t* __restrict__ toff, 
   }
 }
 
-// Workgroup (c, i), i < B (the row i = B takes the offset residues), reads chunk c of encoder i (j in [c kPackChunk, (c + 1) kPackChunk), gridDim.x
-// chunks): shsum[i * 33 + b] += sum_j (v_ij >> b), vmax[i] = max(vmax[i], max_j v_ij) (both start
-// at zero, k_transpose_u32), and the chunk's bit counts c_k = #{j : bit k of v_ij is set} go to
-// ccnt[(i gridDim.x + c) 32 + k].  Since v >> b = sum_{k >= b} bit_k(v) 2^(k - b), the counts give
+// Workgroup (c, i), i < B (the row i = B takes the offset residues), reads chunk c of encoder i (j in
+// [c kPackChunk, (c + 1) kPackChunk), gridDim.x chunks): shsum[i * 33 + b] += sum_j (v_ij >> b), vmax[i] =
+// max(vmax[i], max_j v_ij) (both start at zero, k_transpose_u32), and the chunk's bit counts c_k =
+// #{j : bit k of v_ij is set} go to ccnt[(i gridDim.x + c) 32 + k].  Since v >> b = sum_{k >= b} bit_k(v) 2^(k - b), the counts give
 // sum_j (v_ij >> b) = sum_{k >= b} c_k 2^(k - b) exactly, for any b, here and once the Rice
 // parameters are known (k_chunk_carry).  A thread counts eight bits per add: byte t of cnt8[s]
 // counts bit 8 t + s of its values.
