@@ -1012,8 +1012,9 @@ hipError_t launch_team(SearchArgs& sa, uint64_t items, uint32_t W, size_t lds, h
 //              20 000 (500) 2579/2157/1744/2478; 50 000 (200) 6008/4475/3236/2888; 100 000 (100)
 //              11923/8660/6366/5641
 // Beyond three partitions per CU the one-wavefront time depends on the keys: it is that of the costliest
-// partitions, while a team's launch is bound by the work of all.  Lines are drawn where the fastest of five
-// to seven key sets still gains.  One wavefront, fastest to slowest key set / teams of four, us:
+// partitions, while a team's launch is bound by the work of all.  Lines are drawn where the median of five to
+// seven key sets gains about 5% and the fastest loses no more than that.  One wavefront, fastest to slowest
+// key set / teams of four, us:
 //   P 2500:  lambda 7: 1537 partitions 778-1291/597-738, 1800: 777-962/715-766, 2200: 730-970/798-838, 3072: 809-1205/
 //            1004-1042; lambda 8: 1800 1172-1641/1043-1111, 2200 1123-2226/1114-1260, 3072 1171-1897/1438-1458;
 //            lambda 9: 2200 2310-2954/1906-2078, 2600 2424-3308/2097-2234; lambda 9.8: 3072 5189-5588/3928-4184;
@@ -1036,26 +1037,40 @@ uint32_t team_waves(SearchArgs& sa, uint64_t items) {
     return std::min<uint64_t>(24 / W, sa.lds_limit / size_team_lds(sa, W)) * c;
   };
   if (sa.max_m > kTeamScratchBits) return items <= teams(16) ? 16 : (items <= teams(8) ? 8 : (items <= teams(4) ? 4 : 1));
+  const float p = l * (float)sa.B;
+  const bool full = p <= 2700.0f;  // three or more seeds per part, whose windows fill its lanes
   if (items <= c) return l >= 9.8f ? 16 : 8;
   if (items <= 3 * c) return l >= 11.5f ? 16 : 8;
   if (items <= 6 * c && l >= 10.8f) return 8;
   if (items <= 12 * c) {
     const uint64_t at_once = teams(4);  // 6 c unless the LDS limits it: then a second, nearly empty turn
-    if (at_once < 6 * c && (l < 8.8f ? items > at_once : 5 * items > (l < 9.7f ? 6 : 7) * at_once)) return 1;
+    if (at_once < 6 * c && (l < 8.8f ? items > at_once : 5 * items > 7 * at_once)) return 1;
     if (l >= 9.7f) return 4;
     if (items > 6 * c && l < 6.0f) return 1;
     // where the work of all partitions (items p) takes as long as one partition (its keys p, and a constant)
-    const float s = l < 3.6f   ? 0.3f
-                    : l < 4.6f ? 0.55f
-                    : l < 6.4f ? 0.8f
-                    : l < 8.3f ? 1.0f
-                    : l < 8.8f ? 1.1f
-                    : l < 9.25f ? 1.25f
-                                : 1.6f;
-    return (float)items <= s * (4.3f + 6850.0f / (l * (float)sa.B)) * (float)c ? 4 : 1;
+    float most;
+    if (l < 3.6f)
+      most = 1100.0f;
+    else if (full)
+      most = (1000.0f + 2.55e6f / p) * (l < 4.6f   ? 0.52f
+                                        : l < 6.0f ? 1.0f
+                                        : l < 6.4f ? 0.82f
+                                        : l < 7.8f ? 1.0f
+                                        : l < 8.3f ? 1.14f
+                                        : l < 8.8f ? 1.3f
+                                        : l < 9.25f ? 1.46f
+                                                    : 2.0f);
+    else
+      most = 1600.0f * (l < 4.6f   ? 0.75f
+                        : l < 5.9f ? 0.8f
+                        : l < 6.4f ? 0.9f
+                        : l < 8.3f ? 1.0f
+                        : l < 8.8f ? 1.14f
+                        : l < 9.25f ? 1.42f
+                                    : 1.67f);
+    return (float)items <= most * (float)c / 256.0f ? 4 : 1;
   }
   if (sa.max_m > 4096) return 1;
-  const bool full = l * (float)sa.B <= 2700.0f;
   if (items <= 16 * c) return l >= (full ? 10.0f : 10.8f) ? 4 : 1;
   if (items <= 32 * c) return l >= (full ? 10.8f : 11.8f) ? 4 : 1;
   return full && items <= 64 * c && l >= 11.8f ? 4 : 1;
